@@ -182,6 +182,7 @@ rmsmp_status rmsmp_pack_weights_opt(const float* W, int64_t M, int64_t K, const 
     p->dev.class_rows[t.kind] += t.nvalid;
   }
   p->dev.fp6_taps = h.taps;
+  p->dev.fp6_k = (int32_t)h.K;
   if (e == hipSuccess && up.n_fp6) {
     uint8_t* const fp6 = base + up.n_blob + up.n_tables;
     uint32_t* const bound = up.n_bound ? (uint32_t*)(fp6 + up.n_fp6) : nullptr;

@@ -113,6 +113,7 @@ struct DevicePacked {
   int32_t fp6_steps = 0;   // 64-deep K steps
   int32_t fp6_single = 0;  // tiles stored in one part; the others, with Fixed-8 rows, in two
   int32_t fp6_taps = 1;
+  int32_t fp6_k = 0;       // the layer's K: taps * channels, without padding
 };
 
 // Where weight tile mt lives, computed from DevicePacked alone.

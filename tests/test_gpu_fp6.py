@@ -109,6 +109,34 @@ def test_conv_every_work_group_shape(rm, oracle, shape, geom, M):
         p.free()
 
 
+# convolutions that the FP6 kernels decline where they lie (a tensor below 16 bytes, a side of 65536 and more): the
+# lowered matrix has rows of the padded K, which is not taps * channels
+LOWERED = [((1, 24, 1, 1, 3, 3, 1, 1), 66), ((1, 12, 1, 1, 3, 3, 1, 1), 34), ((1, 6, 2, 2, 2, 2, 1, 0), 64), ((1, 6, 1, 4, 1, 2, 1, 0), 40),
+           ((1, 24, 1, 70000, 1, 9, 200, 0), 34)]
+
+
+@pytest.mark.parametrize("geom,M", LOWERED)
+def test_lowered_matrix_with_padded_columns(rm, oracle, geom, M):
+    B, C, H, Wd, KH, KW, stride, pad = geom
+    rng = np.random.default_rng(sum(geom) + M)
+    K = C * KH * KW
+    W = si.weights_rowscaled(rng, M, K)
+    scheme = si.scheme_permutation(rng, rm.rmsmp_ratio_counts(M, 35, 60, 5))
+    x = si.act_codes_u4(rng, (B, H, Wd, C))
+    bias = rng.normal(0.0, 0.3, M).astype(np.float32)
+    od = oracle.conv_desc(B, C, H, Wd, KH, KW, stride, pad)
+    OH, OW = oracle.conv_out_hw(od)
+    N, z = B * OH * OW, 5
+    ref = oracle.quantize_rows(W, scheme)
+    acc = oracle.conv_acc(ref["wint"].reshape(M, C, KH, KW), x.astype(np.int32), od, zpad=z)
+    p = rm.rmsmp_pack_weights(W, scheme, taps=KH * KW)
+    d = rm.ConvDesc(B, C, H, Wd, KH, KW, stride, pad)
+    X = _to_dev(rm.pack_u4(x))
+    ws = torch.empty((rm.rmsmp_conv2d_workspace_size(p, d, 4),), dtype=torch.uint8, device=DEV)
+    _check_outputs(rm, oracle, lambda Y, ep: rm.rmsmp_conv2d(p, X, d, ep, Y, ws), p, M, N, ref, acc, z, bias, False)
+    p.free()
+
+
 # every column block and a column more and less, K steps that the waves do not share evenly, tiles cut off by the last
 # row, a layer of more than 128 tiles, all row classes
 SKINNY = [(34, 512, 1, (35, 60, 5)), (70, 576, 16, (35, 60, 5)), (64, 1088, 17, (100, 0, 0)), (98, 2112, 32, (0, 100, 0)), (33, 640, 33, (0, 0, 100)),
