@@ -288,8 +288,9 @@ rmsmp_status rmsmp_ste_backward(const float* W, const float* alpha, const float*
  *   applies to every later launch from that thread where it fits the layer (otherwise the
  *   automatic choice stays); all zero returns to the automatic choice.
  *   With pixel_blocks = 0 the request is for the FP6 kernels: k_split = 1..6 a work-group shape of the
- *   tile kernel, 7, 8, 9 the split kernel with 4, 8, 16 waves, 10..13 a work-group shape of the skinny kernel; side_by_side = 1 instead: the
- *   int8 kernels only.
+ *   tile kernel, 7, 8, 9 the split kernel with 4, 8, 16 waves (8 and 9 also for the two layers of a pair),
+ *   10..13 a work-group shape of the skinny kernel; side_by_side = 1 instead: the int8 kernels only
+ *   (a convolution that needs a workspace is then lowered into it), 2: the general kernel only.
  * rmsmp_debug_last_dispatch -- what the calling thread's last rmsmp_gemm / rmsmp_conv2d ran:
  *   out (HOST, 5 entries) = {kernel, pixel_blocks, k_split, side_by_side, tile_pairs} with kernel
  *   0 none, 1 general (4-bit activations: columns that are no multiple of 16 bytes), 2 skinny (N <= 64), 3 small-channel rows, 4 first layer (3 channels,

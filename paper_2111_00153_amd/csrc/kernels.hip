@@ -354,7 +354,8 @@ int launch_gemm(const GemmArgs& a, void* stream) {
     last_dispatch().kernel = 3;
     return launch_conv_rows(a, s);
   }
-  if (!a.conv && a.ep.act_bits == 8) {
+  const bool general_only = forced_general();
+  if (!general_only && !a.conv && a.ep.act_bits == 8) {
     bool applied = false;
     const int rc = try_launch_i8_split(a, stream, &applied);
     if (applied) {
@@ -362,7 +363,7 @@ int launch_gemm(const GemmArgs& a, void* stream) {
       return rc;
     }
   }
-  if (skinny_applies(a)) {
+  if (!general_only && skinny_applies(a)) {
     bool applied = false;
     const int rc = try_launch_skinny(a, stream, &applied);
     if (applied) {
@@ -370,12 +371,12 @@ int launch_gemm(const GemmArgs& a, void* stream) {
       return rc;
     }
   }
-  if (forced_split()[0] == 0 && forced_split()[2] == 0) {
+  {
     bool applied = false;
     const int rc = try_launch_fp6(a, stream, &applied);
     if (applied) return rc;
   }
-  {
+  if (!general_only) {
     bool applied = false;
     const int rc = try_launch_wide(a, stream, &applied);
     if (applied) return rc;

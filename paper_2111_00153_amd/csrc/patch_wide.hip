@@ -255,7 +255,7 @@ int try_launch_wide_pair(const GemmArgs& a0, const GemmArgs& b0, void* stream, b
   *applied = false;
   GemmArgs a, b;
   int cca = 0, ccb = 0;
-  if (a0.X != b0.X || !a0.conv || !b0.conv) return 0;
+  if (a0.X != b0.X || !a0.conv || !b0.conv || forced_general()) return 0;
   if (a0.ep.out_kind == 3 || b0.ep.out_kind == 3) return 0;
   if (!wide_layer_fits(a0, &a, &cca) || !wide_layer_fits(b0, &b, &ccb)) return 0;
   if (a.d.KH * a.d.KW != 9 || b.d.KH * b.d.KW != 1) return 0;

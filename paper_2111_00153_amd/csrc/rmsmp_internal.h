@@ -181,13 +181,17 @@ int launch_ste_backward(const SteArgs& a, void* stream);
 
 // Test hooks.  forced_split(): a wave split {pixel blocks per wave, K split, pixel blocks side by
 // side, tile pairs} the LDS-resident kernel should use where it fits the layer (all zero:
-// automatic); like last_dispatch() it belongs to the calling thread.
+// automatic); like last_dispatch() it belongs to the calling thread.  Without a wave split (first entry 0) the
+// second entry is a work-group shape of the FP6 or the skinny kernel, the third 1 for the int8 kernels
+// only and 2 for the general kernel only.
 // last_dispatch(): which kernel the calling thread's last launch_gemm went to.
 struct DispatchRecord {
   int kernel = 0;  // 0 none, 1 general, 2 skinny, 3 small-channel rows, 4 first layer, 5 LDS-resident, 6 LDS-resident, two layers in one launch
   int xb = 0, ks = 0, nwt = 0, ms = 0;
 };
 int* forced_split();
+inline bool forced_off_fp6() { return forced_split()[0] != 0 || forced_split()[2] != 0; }
+inline bool forced_general() { return forced_split()[0] == 0 && forced_split()[2] == 2; }
 DispatchRecord& last_dispatch();
 
 // Kernel launchers (kernels.hip).  Return hipError_t as int.

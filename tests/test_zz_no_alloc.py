@@ -24,8 +24,9 @@ def _dev(a):
     return torch.from_numpy(np.ascontiguousarray(a)).to(DEV)
 
 
-def _both_ways(rm, B, C, H, M, k, stride, pad, seed):
-    """All three output kinds of one layer through both entry points; returns the workspace size."""
+def _both_ways(rm, B, C, H, M, k, stride, pad, seed, lowered):
+    """All three output kinds of one layer through both entry points; returns the workspace size.  lowered: whether the
+    matrix is to be found in the caller's workspace afterwards."""
     rng = np.random.default_rng(seed)
     K = C * k * k
     W = si.weights_rowscaled(rng, M, K)
@@ -44,23 +45,31 @@ def _both_ways(rm, B, C, H, M, k, stride, pad, seed):
         ep = rm.make_epilogue(0.05, 3, 4, None if kind == rm.OUT_INT32 else bias, kind != rm.OUT_INT32, kind, 1.7)
         Ya = torch.zeros(shape, dtype=dtype, device=DEV)
         Yb = torch.ones(shape, dtype=dtype, device=DEV)
+        ws.fill_(0xA5)
         rm.rmsmp_conv2d(p, X, d, ep, Ya, ws if need else None)
         rm.rmsmp_conv2d_static_workspace(p, X, d, ep, Yb)
         torch.cuda.synchronize()
         assert torch.equal(Ya, Yb), (kind, B, C, H)
+        assert bool((ws != 0xA5).any()) == lowered
     p.free()
     return need
 
 
-def test_static_workspace_matches_caller_workspace_twice(rm):
+# 0: the library's choice, which reads such a layer where it lies; 1 and 2: the int8 kernels, the general kernel
+@pytest.mark.parametrize("kernels", [0, 1, 2])
+def test_static_workspace_matches_caller_workspace_twice(rm, kernels):
     rm.rmsmp_init()
-    # 24 input channels: not a multiple of 16, so the lowered matrix goes through the workspace
-    big = _both_ways(rm, 3, 24, 20, 96, 3, 1, 1, seed=1)
-    assert 0 < big <= rm.STATIC_WORKSPACE_BYTES
-    small = _both_ways(rm, 1, 24, 9, 96, 3, 2, 1, seed=2)
-    assert 0 < small < big
-    # a layer that needs no workspace passes straight through
-    assert _both_ways(rm, 2, 64, 10, 64, 3, 1, 1, seed=3) == 0
+    rm.rmsmp_debug_set_wave_split(0, 0, kernels, 0)
+    try:
+        # 24 input channels: not a multiple of 16, so the lowered matrix goes through the workspace
+        big = _both_ways(rm, 3, 24, 20, 96, 3, 1, 1, 1, kernels != 0)
+        assert 0 < big <= rm.STATIC_WORKSPACE_BYTES
+        small = _both_ways(rm, 1, 24, 9, 96, 3, 2, 1, 2, kernels != 0)
+        assert 0 < small < big
+        # a layer that needs no workspace passes straight through
+        assert _both_ways(rm, 2, 64, 10, 64, 3, 1, 1, 3, False) == 0
+    finally:
+        rm.rmsmp_debug_set_wave_split(0, 0, 0, 0)
 
 
 def test_static_workspace_refuses_what_does_not_fit(rm):
