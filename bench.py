@@ -108,8 +108,13 @@ def kernel_of(rm, layer):
     layer["launch"]()
     kernel, split = rm.rmsmp_debug_last_dispatch()
     taps, cpt = layer["k"] * layer["k"], layer["C"] // 32
+    flags = tuple("true" if split[3] & bit else "false" for bit in (1, 2))
     if kernel == "lds_resident":
         return "rmsmp::conv_wide_kernel<%d, %d, %d, %d, %d, %d, false>" % ((taps, cpt) + split)
+    if kernel == "fp6_tile":
+        return "rmsmp::fp6_tile_kernel<%d, %d, %d, %s, %s>" % (split[:3] + flags)
+    if kernel == "fp6_split":
+        return "rmsmp::fp6_split_kernel<%d, %s, %s>" % (split[:1] + flags)
     if kernel == "first_layer":
         return "rmsmp::conv_first_kernel"
     return kernel
@@ -510,9 +515,10 @@ def main():
     for u in units:
         if len(u["layers"]) == 2:
             u["launch"]()
-            kernel, _ = rm.rmsmp_debug_last_dispatch()
-            if kernel == "lds_resident_pair":
-                u["kernel"] = "rmsmp::conv_wide_pair_kernel<%d>" % (u["layers"][0]["C"] // 32)
+            kernel, numbers = rm.rmsmp_debug_last_dispatch()
+            if kernel in ("lds_resident_pair", "fp6_split_pair"):
+                u["kernel"] = ("rmsmp::conv_wide_pair_kernel<%d>" % (u["layers"][0]["C"] // 32) if kernel == "lds_resident_pair"
+                               else "rmsmp::fp6_split_pair_kernel<%d>" % numbers[0])
                 u["us"] = time_block(torch, [u["launch"]], args.layer_iters, 10)
                 a, b = u["layers"]
                 fused[a["name"] + " + " + b["name"]] = dict(us=round(u["us"], 3), one_after_the_other_us=round(a["us"] + b["us"], 3),

@@ -291,11 +291,18 @@ rmsmp_status rmsmp_ste_backward(const float* W, const float* alpha, const float*
  *   tile kernel, 7, 8, 9 the split kernel with 4, 8, 16 waves (8 and 9 also for the two layers of a pair),
  *   10..13 a work-group shape of the skinny kernel; side_by_side = 1 instead: the int8 kernels only
  *   (a convolution that needs a workspace is then lowered into it), 2: the general kernel only.
- * rmsmp_debug_last_dispatch -- what the calling thread's last rmsmp_gemm / rmsmp_conv2d ran:
- *   out (HOST, 5 entries) = {kernel, pixel_blocks, k_split, side_by_side, tile_pairs} with kernel
- *   0 none, 1 general (4-bit activations: columns that are no multiple of 16 bytes), 2 skinny (N <= 64), 3 small-channel rows, 4 first layer (3 channels,
- *   stride 2), 5 LDS-resident, 6 LDS-resident with two layers in one launch (rmsmp_conv2d_pair);
- *   the other four are 0 unless kernel == 5.
+ * rmsmp_debug_last_dispatch -- what the calling thread's last rmsmp_gemm / rmsmp_conv2d /
+ *   rmsmp_conv2d_pair ran (a pair that went out as two launches: the second one):
+ *   out (HOST, 5 entries) = {kernel, a, b, c, d} with kernel
+ *   0 none, 1 general, 2 skinny (N <= 64), 3 small-channel rows, 4 first layer (3 channels, stride 2),
+ *   5 LDS-resident: a, b, c, d = pixel_blocks, k_split, side_by_side, tile_pairs,
+ *   6 LDS-resident with two layers in one launch (rmsmp_conv2d_pair),
+ *   7 FP6 tile: 32-column blocks per wave, waves along the rows, waves along the columns, variant,
+ *   8 FP6 split: waves, 0, 0, variant,
+ *   9 FP6 split with two layers in one launch: as 8,
+ *   10 split on int8 instructions (8-bit activations): as 8;
+ *   variant: 1 for a convolution, plus 2 where a column (pixel) is no multiple of 16 bytes.  What
+ *   is not named is 0.
  * Errors: EINVAL (negative value, NULL).
  */
 rmsmp_status rmsmp_debug_set_wave_split(int32_t pixel_blocks, int32_t k_split, int32_t side_by_side,

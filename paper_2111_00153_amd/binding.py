@@ -317,11 +317,12 @@ def rmsmp_debug_set_wave_split(pixel_blocks=0, k_split=0, side_by_side=0, tile_p
     _check(_lib.rmsmp_debug_set_wave_split(int(pixel_blocks), int(k_split), int(side_by_side), int(tile_pairs)))
 
 
-KERNEL_NAMES = ("none", "general", "skinny", "rows", "first_layer", "lds_resident", "lds_resident_pair")
+KERNEL_NAMES = ("none", "general", "skinny", "rows", "first_layer", "lds_resident", "lds_resident_pair", "fp6_tile", "fp6_split", "fp6_split_pair",
+                "int8_split")
 
 
 def rmsmp_debug_last_dispatch():
-    """(kernel name, (pixel_blocks, k_split, side_by_side, tile_pairs)) of this thread's last launch."""
+    """(kernel name, four numbers as include/rmsmp.h describes them for that kernel) of this thread's last launch."""
     out = (ctypes.c_int32 * 5)()
     _check(_lib.rmsmp_debug_last_dispatch(out))
     return KERNEL_NAMES[out[0]], tuple(int(v) for v in out[1:])

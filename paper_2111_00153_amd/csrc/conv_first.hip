@@ -455,7 +455,7 @@ static int launch_conv_first_t(const GemmArgs& a, const FirstGeom& g, unsigned b
 int try_launch_conv_first(const GemmArgs& a, void* stream, bool* applied) {
   *applied = conv_first_applies(a);
   if (!*applied) return 0;
-  last_dispatch() = DispatchRecord{4, 0, 0, 0, 0};
+  last_dispatch() = DispatchRecord{DK_FIRST_LAYER};
   FirstGeom g;
   g.tiles_w = (a.OW + CF_T - 1) / CF_T;
   g.tiles_h = (a.OH + CF_T - 1) / CF_T;

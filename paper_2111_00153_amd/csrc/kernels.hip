@@ -351,23 +351,20 @@ int launch_gemm(const GemmArgs& a, void* stream) {
     if (applied) return rc;
   }
   if (conv_rows_applies(a)) {
-    last_dispatch().kernel = 3;
+    last_dispatch().kernel = DK_ROWS;
     return launch_conv_rows(a, s);
   }
   const bool general_only = forced_general();
   if (!general_only && !a.conv && a.ep.act_bits == 8) {
     bool applied = false;
     const int rc = try_launch_i8_split(a, stream, &applied);
-    if (applied) {
-      last_dispatch().kernel = 1;
-      return rc;
-    }
+    if (applied) return rc;
   }
   if (!general_only && skinny_applies(a)) {
     bool applied = false;
     const int rc = try_launch_skinny(a, stream, &applied);
     if (applied) {
-      last_dispatch().kernel = 2;
+      last_dispatch().kernel = DK_SKINNY;
       return rc;
     }
   }
@@ -381,7 +378,7 @@ int launch_gemm(const GemmArgs& a, void* stream) {
     const int rc = try_launch_wide(a, stream, &applied);
     if (applied) return rc;
   }
-  last_dispatch().kernel = 1;
+  last_dispatch().kernel = DK_GENERAL;
   if (a.conv) return a.ep.act_bits == 4 ? launch_general<4, true, true>(a, s) : launch_general<8, true, true>(a, s);
   const bool vec = (a.K % 16) == 0;
   if (a.ep.act_bits == 4) return vec ? launch_general<4, false, true>(a, s) : launch_general<4, false, false>(a, s);

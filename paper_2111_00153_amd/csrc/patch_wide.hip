@@ -241,9 +241,7 @@ int try_launch_wide(const GemmArgs& a, void* stream, bool* applied) {
     if (wide_plan_mode(plan.a, plan.cpt * KSTEP, forced[0], forced[1], forced[2], forced[3], &p2)) plan = p2;
   }
   if (!*applied) return 0;
-  DispatchRecord& rec = last_dispatch();
-  rec.kernel = 5;
-  rec.xb = plan.xb, rec.ks = plan.ks, rec.nwt = plan.nwt, rec.ms = plan.ms;
+  last_dispatch() = DispatchRecord{DK_LDS_RESIDENT, plan.xb, plan.ks, plan.nwt, plan.ms};
   return launch_wide(plan, (hipStream_t)stream);
 }
 
@@ -269,9 +267,7 @@ int try_launch_wide_pair(const GemmArgs& a0, const GemmArgs& b0, void* stream, b
   if (!wide_plan_mode(a, cca, sp.xa, sp.ka, sp.na, sp.ma, &pa) || !wide_plan_mode(b, ccb, sp.xb, sp.kb, sp.nb, sp.mb, &pb)) return 0;
   if ((uint64_t)pa.blocks + pb.blocks > 0x7fffffffu) return 0;
   *applied = true;
-  DispatchRecord& rec = last_dispatch();
-  rec.kernel = 6;
-  rec.xb = 0, rec.ks = 0, rec.nwt = 0, rec.ms = 0;
+  last_dispatch() = DispatchRecord{DK_LDS_RESIDENT_PAIR};
 #define RMSMP_WIDE_CASE(CP) \
   if (cpt == CP) return launch_wide_pair_##CP(pa, pb, (hipStream_t)stream);
   RMSMP_WIDE_PAIR_FAMILIES(RMSMP_WIDE_CASE)

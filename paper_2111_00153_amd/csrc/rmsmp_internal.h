@@ -184,9 +184,15 @@ int launch_ste_backward(const SteArgs& a, void* stream);
 // automatic); like last_dispatch() it belongs to the calling thread.  Without a wave split (first entry 0) the
 // second entry is a work-group shape of the FP6 or the skinny kernel, the third 1 for the int8 kernels
 // only and 2 for the general kernel only.
-// last_dispatch(): which kernel the calling thread's last launch_gemm went to.
+// last_dispatch(): which kernel the calling thread's last call of the library went to; whoever launches writes all of it.
+enum DispatchKernel {
+  DK_NONE = 0, DK_GENERAL = 1, DK_SKINNY = 2, DK_ROWS = 3, DK_FIRST_LAYER = 4, DK_LDS_RESIDENT = 5, DK_LDS_RESIDENT_PAIR = 6,
+  DK_FP6_TILE = 7, DK_FP6_SPLIT = 8, DK_FP6_SPLIT_PAIR = 9, DK_INT8_SPLIT = 10
+};
 struct DispatchRecord {
-  int kernel = 0;  // 0 none, 1 general, 2 skinny, 3 small-channel rows, 4 first layer, 5 LDS-resident, 6 LDS-resident, two layers in one launch
+  int kernel = DK_NONE;
+  // LDS-resident: the wave split.  FP6 tile: column blocks per wave, waves along the rows, waves along the columns,
+  // kernel variant (1 convolution + 2 ragged columns).  Split kernels: waves, 0, 0, variant.
   int xb = 0, ks = 0, nwt = 0, ms = 0;
 };
 int* forced_split();

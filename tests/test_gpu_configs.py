@@ -272,11 +272,12 @@ def test_remaining_inference_gemms(rm, oracle, name, M, K, N, ratio, bits):
 # ---- GELU epilogue of the feed-forward up-projection (out_kind 3)
 
 @pytest.mark.parametrize("M,K,N,inv_s,z_out,with_bias", [
-    (3072, 768, 4096, 2.0, 1, True),      # configs[2]'s shape: the LDS-resident kernel
+    (3072, 768, 4096, 2.0, 1, True),      # a feed-forward up-projection over 4096 tokens
     (3072, 768, 4096, 6.5, 2, False),     # a finer output scale: codes below the zero point on GELU's negative lobe
-    (130, 576, 300, 6.0, 0, True),        # general kernel, ragged tiles
-    (96, 1024, 8, 5.0, 1, True),          # skinny kernel
+    (130, 576, 300, 6.0, 0, True),        # ragged tiles
+    (96, 1024, 8, 5.0, 1, True),          # few columns
 ])
+@pytest.mark.usefixtures("kernels")
 def test_gelu_epilogue_matches_oracle(rm, oracle, M, K, N, inv_s, z_out, with_bias):
     """BERT-base FFN up-projection with the GELU + affine 4-bit requantization fused: every 4-bit code
     against the oracle (GELU in float64 from the same fp32 pre-activation)."""
@@ -300,6 +301,7 @@ def test_gelu_epilogue_matches_oracle(rm, oracle, M, K, N, inv_s, z_out, with_bi
     p.free()
 
 
+@pytest.mark.usefixtures("kernels")
 def test_gelu_epilogue_conv_and_argument_errors(rm, oracle):
     """The same epilogue behind rmsmp_conv2d (1x1 and 3x3), and the argument checks of out_kind 3."""
     rng = np.random.default_rng(77)

@@ -24,6 +24,17 @@ def rm():
     m.rmsmp_debug_set_wave_split(0, 0, 0, 0)
 
 
+# what to ask the dispatch hook for
+CHOSEN, INT8, GENERAL = (0, 0, 0, 0), (0, 0, 1, 0), (0, 0, 2, 0)
+
+
+@pytest.fixture
+def only(rm):
+    """only(request): every later launch of the test; back to the library's choice afterwards."""
+    yield lambda request: rm.rmsmp_debug_set_wave_split(*request)
+    rm.rmsmp_debug_set_wave_split(*CHOSEN)
+
+
 def _to_dev(a):
     return torch.from_numpy(np.ascontiguousarray(a)).to(DEV)
 
@@ -178,8 +189,9 @@ def test_lds_resident_kernel_deep_gemm_every_wave_split(rm, oracle, split, M, K,
         p.free()
 
 
-def test_lds_resident_kernel_deep_1x1_layer(rm, oracle):
+def test_lds_resident_kernel_deep_1x1_layer(rm, oracle, only):
     """A 1x1 layer of stride 1 with 1024 input channels (a ResNet-50 bottleneck's shape): two parts of 512."""
+    only(INT8)
     _check_conv(rm, oracle, (2, 1024, 7, 9, 1, 1, 1, 0), 96, (35, 60, 5), 4, 5, True, True, 41, "lds_resident")
 
 
@@ -206,9 +218,11 @@ def test_first_layer_kernel_several_tiles_per_work_group(rm, oracle, B, k, pad):
     _check_conv(rm, oracle, geom, 40, (35, 60, 5), 8, 2, True, True, 32, "first_layer")
 
 
-def test_gemm_with_k_of_a_lowered_3x3_layer_four_bit_output(rm, oracle):
-    """K = 576 = 9 x 64 through the 3x3 family, 4-bit output with bias and ReLU and without (the lean
-    epilogue), ragged N."""
+@pytest.mark.parametrize("request_,want", [(INT8, "lds_resident"), (GENERAL, "general"), ((0, 4, 0, 0), "fp6_tile"), ((0, 8, 0, 0), "fp6_split")])
+def test_gemm_with_k_of_a_lowered_3x3_layer_four_bit_output(rm, oracle, only, request_, want):
+    """K = 576 = 9 x 64 through the 3x3 family of the LDS-resident kernel and through the others that take it, 4-bit
+    output with bias and ReLU and without (the lean epilogue), ragged N."""
+    only(request_)
     rng = np.random.default_rng(576)
     M, K, N = 96, 576, 333
     W = si.weights_rowscaled(rng, M, K)
@@ -225,35 +239,84 @@ def test_gemm_with_k_of_a_lowered_3x3_layer_four_bit_output(rm, oracle):
         _, _, q = oracle.epilogue(acc, oracle.rowsum(ref["wint"]), z, ref["rowscale"], 0.05, bias, True, inv)
         Yq = torch.full((N, M // 2), 0xEE, dtype=torch.uint8, device=DEV)
         rm.rmsmp_gemm(p, X, N, rm.make_epilogue(0.05, z, 4, None if bias is None else _to_dev(bias), True, rm.OUT_U4, inv), Yq)
-        assert rm.rmsmp_debug_last_dispatch()[0] == "lds_resident"
+        assert rm.rmsmp_debug_last_dispatch()[0] == want
         torch.cuda.synchronize()
         assert np.array_equal(_grouped_codes(rm, Yq.cpu().numpy(), p.perm), q)
     p.free()
 
 
-def test_dispatch_record_names_the_kernel(rm, oracle):
-    """The dispatch hook reports the kernel family of the last launch on this thread."""
+# (M, K, N, bits of the activations, request, kernel and its four numbers where they do not depend on a cost estimate)
+RECORDS = [(64, 4096, 8, 4, CHOSEN, "skinny", (0, 0, 0, 0)), (64, 512, 256, 4, INT8, "lds_resident", None), (64, 576, 256, 4, INT8, "lds_resident", None),
+           (37, 130, 77, 4, INT8, "general", (0, 0, 0, 0)), (64, 512, 256, 4, GENERAL, "general", (0, 0, 0, 0)), (64, 4096, 8, 4, GENERAL, "general", (0, 0, 0, 0)),
+           (64, 512, 256, 4, (0, 1, 0, 0), "fp6_tile", (4, 4, 1, 0)), (64, 576, 256, 4, (0, 6, 0, 0), "fp6_tile", (1, 1, 4, 0)),
+           (37, 130, 77, 4, (0, 2, 0, 0), "fp6_tile", (2, 2, 2, 2)), (64, 512, 256, 4, (0, 7, 0, 0), "fp6_split", (4, 0, 0, 0)),
+           (37, 130, 77, 4, (0, 9, 0, 0), "fp6_split", (16, 0, 0, 2)), (37, 130, 77, 4, CHOSEN, "fp6_split", None), (64, 576, 256, 4, CHOSEN, "fp6_split", None),
+           (768, 768, 8192, 4, CHOSEN, "fp6_tile", None), (64, 512, 40, 8, CHOSEN, "int8_split", (8, 0, 0, 0)), (64, 2050, 40, 8, CHOSEN, "int8_split", (16, 0, 0, 2)),
+           (64, 512, 40, 8, GENERAL, "general", (0, 0, 0, 0)), (64, 512, 40000, 8, CHOSEN, "general", (0, 0, 0, 0))]
+
+
+@pytest.mark.parametrize("M,K,N,bits,request_,want,numbers", RECORDS)
+def test_dispatch_record_names_the_kernel(rm, oracle, only, M, K, N, bits, request_, want, numbers):
+    """The dispatch hook reports the kernel of the last launch on this thread, and the kernel is right."""
     rng = np.random.default_rng(5)
-    for (M, K, N, want) in [(64, 4096, 8, "skinny"), (64, 512, 256, "lds_resident"), (64, 576, 256, "lds_resident"),
-                            (37, 130, 77, "general")]:
-        W = si.weights_rowscaled(rng, M, K)
-        scheme = si.scheme_permutation(rng, rm.rmsmp_ratio_counts(M, 35, 60, 5))
-        xq = si.act_codes_u4(rng, (N, K))
-        p = rm.rmsmp_pack_weights(W, scheme)
-        Y = torch.empty((M, N), dtype=torch.int32, device=DEV)
-        rm.rmsmp_gemm(p, _to_dev(rm.pack_u4(xq)), N, rm.make_epilogue(0.05, 0, 4, None, False, rm.OUT_INT32), Y)
-        assert rm.rmsmp_debug_last_dispatch()[0] == want
-        torch.cuda.synchronize()
-        ref = oracle.quantize_rows(W, scheme)
-        assert np.array_equal(Y.cpu().numpy(), oracle.gemm_acc(ref["wint"], xq.astype(np.int32)))
+    only(request_)
+    W = si.weights_rowscaled(rng, M, K)
+    scheme = si.scheme_permutation(rng, rm.rmsmp_ratio_counts(M, 35, 60, 5))
+    xq = si.act_codes_u4(rng, (N, K)) if bits == 4 else si.act_codes_i8(rng, (N, K))
+    p = rm.rmsmp_pack_weights(W, scheme)
+    Y = torch.empty((M, N), dtype=torch.int32, device=DEV)
+    rm.rmsmp_gemm(p, _to_dev(rm.pack_u4(xq) if bits == 4 else xq), N, rm.make_epilogue(0.05, 0, bits, None, False, rm.OUT_INT32), Y)
+    kernel, got = rm.rmsmp_debug_last_dispatch()
+    assert kernel == want and (numbers is None or got == numbers), (kernel, got)
+    torch.cuda.synchronize()
+    ref = oracle.quantize_rows(W, scheme)
+    cols = slice(None) if N < 10000 else slice(N - 300, N)
+    assert np.array_equal(Y[:, cols].cpu().numpy(), oracle.gemm_acc(ref["wint"], xq[cols].astype(np.int32)))
+    p.free()
+
+
+def test_dispatch_record_of_convolutions(rm, only):
+    """Convolutions that are read where they lie whatever their width, and pairs, write the whole record: nothing of an
+    earlier launch stays in it."""
+    rng = np.random.default_rng(6)
+
+    def layer(C, M, k, s, H):
+        p = rm.rmsmp_pack_weights(si.weights_rowscaled(rng, M, C * k * k), np.zeros(M, np.uint8), taps=k * k)
+        d = rm.ConvDesc(2, C, H, H, k, k, s, k // 2)
+        o = (H + 2 * (k // 2) - k) // s + 1
+        need = rm.rmsmp_conv2d_workspace_size(p, d, 4)
+        return p, d, torch.empty((M, 2 * o * o), dtype=torch.int32, device=DEV), torch.empty(max(need, 1), dtype=torch.uint8, device=DEV)
+
+    ep = rm.make_epilogue(0.05, 0, 4, None, False, rm.OUT_INT32)
+    for C, request_, want in [(64, (4, 1, 4, 1), ("lds_resident", (4, 1, 4, 1))), (24, (0, 8, 0, 0), ("fp6_split", (8, 0, 0, 3))),
+                              (64, (4, 1, 4, 1), ("lds_resident", (4, 1, 4, 1))), (24, (0, 3, 0, 0), ("fp6_tile", (2, 1, 4, 3))),
+                              (96, (0, 9, 0, 0), ("fp6_split", (16, 0, 0, 1))), (96, INT8, ("general", (0, 0, 0, 0)))]:
+        p, d, Y, ws = layer(C, 64, 3, 1, 12)
+        only(request_)
+        rm.rmsmp_conv2d(p, torch.zeros((2, 12, 12, C // 2), dtype=torch.uint8, device=DEV), d, ep, Y, ws)
+        assert rm.rmsmp_debug_last_dispatch() == want
+        p.free()
+    X = torch.zeros((2, 12, 12, 32), dtype=torch.uint8, device=DEV)
+    (pa, da, Ya, _), (pb, db, Yb, _), (pc, dc, Yc, _) = layer(64, 128, 3, 2, 12), layer(64, 128, 1, 2, 12), layer(64, 64, 3, 1, 12)
+    for request_, want in [((0, 8, 0, 0), ("fp6_split_pair", (8, 0, 0, 1))), ((0, 9, 0, 0), ("fp6_split_pair", (16, 0, 0, 1))),
+                           (INT8, ("lds_resident_pair", (0, 0, 0, 0))), (GENERAL, ("general", (0, 0, 0, 0)))]:
+        only((4, 1, 4, 1))
+        rm.rmsmp_conv2d(pc, X, dc, ep, Yc)
+        assert rm.rmsmp_debug_last_dispatch() == ("lds_resident", (4, 1, 4, 1))
+        only(request_)
+        rm.rmsmp_conv2d_pair(pa, da, ep, Ya, pb, db, ep, Yb, X)
+        assert rm.rmsmp_debug_last_dispatch() == want
+    torch.cuda.synchronize()
+    for p in (pa, pb, pc):
         p.free()
 
 
 @pytest.mark.parametrize("ratio", [(35, 60, 5), (100, 0, 0)])
-def test_pot_rows_stored_as_int8_give_the_same_results(rm, oracle, ratio):
+def test_pot_rows_stored_as_int8_give_the_same_results(rm, oracle, only, ratio):
     """RMSMP_PACK_POT_AS_INT8: PoT-4 rows stored decoded.  Codes, scales, row sums, accumulators and
     4-bit outputs are those of the oracle (and so of the 4-bit storage) through the LDS-resident, the
     skinny and the general kernel."""
+    only(INT8)
     rng = np.random.default_rng(800 + ratio[0])
     # a 3x3 layer (LDS-resident kernel)
     B, C, H, M = 3, 128, 12, 160

@@ -87,7 +87,16 @@ def _pair(rm, oracle, seed, B, C, H, W, MA, MB, stride, z, bias_a=False, bias_b=
     return _to_dev(rm.pack_u4(x)), A, Bl
 
 
-def _run_all_kinds(rm, X, A, Bl, z, expect_kernel):
+def _run_all_kinds(rm, X, A, Bl, z, expect_kernel, split=(0, 0, 1, 0)):
+    """split: what to ask the dispatch hook for (the int8 kernels unless the test says otherwise)."""
+    rm.rmsmp_debug_set_wave_split(*split)
+    try:
+        _all_kinds(rm, X, A, Bl, z, expect_kernel)
+    finally:
+        rm.rmsmp_debug_set_wave_split(0, 0, 0, 0)
+
+
+def _all_kinds(rm, X, A, Bl, z, expect_kernel):
     for ka, kb in ((rm.OUT_U4, rm.OUT_U4), (rm.OUT_INT32, rm.OUT_FP32), (rm.OUT_FP32, rm.OUT_INT32), (rm.OUT_U4, rm.OUT_FP32)):
         Ya, Yb = A.output(rm, ka), Bl.output(rm, kb)
         rm.rmsmp_conv2d_pair(A.p, A.d, A.epilogue(rm, z, ka), Ya, Bl.p, Bl.d, Bl.epilogue(rm, z, kb), Yb, X)
@@ -107,6 +116,9 @@ def test_pair_runs_as_one_launch_and_matches_oracle(rm, oracle, C, MA, MB, H, W,
     z = 3
     X, A, Bl = _pair(rm, oracle, 1000 + C + stride, 3, C, H, W, MA, MB, stride, z)
     _run_all_kinds(rm, X, A, Bl, z, "lds_resident_pair")
+    # the split kernel of the FP6 path with 8 and with 16 waves per work-group (a 1x1 layer of stride 1 is a GEMM there)
+    for waves in ((0, 8, 0, 0), (0, 9, 0, 0)):
+        _run_all_kinds(rm, X, A, Bl, z, "fp6_split_pair" if stride == 2 else "lds_resident_pair", waves)
     A.p.free()
     Bl.p.free()
 
@@ -116,6 +128,7 @@ def test_pair_of_resnet_stage_head_shapes(rm, oracle):
     no bias, ReLU on the 3x3 layer only: the configuration bench.py launches."""
     X, A, Bl = _pair(rm, oracle, 77, 2, 128, 28, 28, 256, 256, 2, 0, bias_a=False, bias_b=False)
     _run_all_kinds(rm, X, A, Bl, 0, "lds_resident_pair")
+    _run_all_kinds(rm, X, A, Bl, 0, "fp6_split_pair", (0, 0, 0, 0))
     A.p.free()
     Bl.p.free()
 
@@ -124,9 +137,8 @@ def test_pair_falls_back_to_two_launches(rm, oracle):
     """Shapes the two-layer launch does not exist for are launched one after the other, with the
     same results: 96 channels (general kernel), and two 3x3 layers."""
     X, A, Bl = _pair(rm, oracle, 5, 2, 96, 12, 12, 64, 64, 2, 1)
-    _run_all_kinds(rm, X, A, Bl, 1, None)
-    kernel, _ = rm.rmsmp_debug_last_dispatch()
-    assert kernel != "lds_resident_pair"
+    _run_all_kinds(rm, X, A, Bl, 1, "general")
+    _run_all_kinds(rm, X, A, Bl, 1, "fp6_split", (0, 0, 0, 0))
     A.p.free()
     Bl.p.free()
     X, A, Bl = _pair(rm, oracle, 6, 2, 64, 12, 12, 128, 128, 1, 0, kb=3)

@@ -99,6 +99,7 @@ def test_one_hot_activations_return_the_weights(rm, oracle):
     p.free()
 
 
+@pytest.mark.usefixtures("kernels")
 @pytest.mark.parametrize("M,K,N", [(64, 576, 256), (37, 130, 77), (16, 64, 1), (130, 1000, 65), (2, 2, 3),
                                    (272, 192, 200), (100, 2304, 129)])
 @pytest.mark.parametrize("ratio", [(35, 60, 5), (100, 0, 0), (0, 100, 0), (0, 0, 100), (50, 50, 0)])
@@ -115,6 +116,7 @@ def test_gemm_ragged_shapes_and_ratios(rm, oracle, M, K, N, ratio):
     p.free()
 
 
+@pytest.mark.usefixtures("kernels")
 @pytest.mark.parametrize("M,K,N", [(64, 576, 256), (38, 130, 77), (256, 256, 100)])
 def test_gemm_bias_relu_requant_grouped_output(rm, oracle, M, K, N):
     rng = np.random.default_rng(M + K + N)
@@ -136,6 +138,7 @@ def test_gemm_bias_relu_requant_grouped_output(rm, oracle, M, K, N):
     p.free()
 
 
+@pytest.mark.usefixtures("kernels")
 @pytest.mark.parametrize("M,K,N", [(70, 64, 129), (130, 128, 300), (2000, 256, 5000), (96, 512, 1000), (333, 768, 257), (1030, 768, 4100),
                                    (33, 768, 128)])
 def test_gemm_lds_resident_activation_kernel(rm, oracle, M, K, N):
@@ -161,6 +164,7 @@ def test_gemm_lds_resident_activation_kernel(rm, oracle, M, K, N):
     p.free()
 
 
+@pytest.mark.usefixtures("kernels")
 def test_gemm_int8_activations(rm, oracle):
     rng = np.random.default_rng(31)
     for M, K, N in [(64, 147, 300), (32, 256, 64)]:
@@ -213,6 +217,7 @@ def run_conv(rm, oracle, geom, M, ratio, act_bits=4, z=0, relu=False, requant=Fa
     return ws_bytes
 
 
+@pytest.mark.usefixtures("kernels")
 @pytest.mark.parametrize("geom", [(2, 64, 6, 6, 3, 3, 1, 1), (1, 128, 9, 7, 3, 3, 2, 1), (3, 64, 8, 8, 1, 1, 2, 0),
                                   (2, 256, 5, 5, 3, 3, 1, 1), (2, 96, 5, 5, 3, 3, 1, 1), (1, 16, 9, 9, 5, 5, 2, 2),
                                   (2, 32, 6, 5, 3, 3, 1, 2)])
@@ -222,18 +227,20 @@ def test_conv_implicit_im2col(rm, oracle, geom):
     run_conv(rm, oracle, geom, 34, (35, 60, 5), z=6, seed=1)
 
 
+@pytest.mark.usefixtures("kernels")
 @pytest.mark.parametrize("geom", [(5, 64, 14, 14, 3, 3, 1, 1), (2, 128, 10, 9, 3, 3, 1, 0), (3, 64, 7, 7, 1, 1, 1, 0),
                                   (1, 64, 40, 40, 3, 3, 1, 1), (9, 128, 7, 7, 3, 3, 1, 1), (1, 64, 1, 1, 1, 1, 1, 0),
                                   (2, 512, 7, 7, 3, 3, 1, 1)])
 @pytest.mark.parametrize("M", [48, 256, 90])
 def test_conv_stride1_lds_patch_kernel(rm, oracle, geom, M):
-    """Stride-1 layers with C % 64 == 0 take the LDS-resident patch kernel: several pixel tiles,
+    """Stride-1 layers with C % 64 == 0, which the LDS-resident patch kernel is made for: several pixel tiles,
     tiles that straddle images, a ragged last tile, no padding, 1x1, partial weight tiles."""
     z = (sum(geom) + M) % 16
     assert run_conv(rm, oracle, geom, M, (35, 60, 5), z=z, relu=True, requant=True, seed=3) == 0
     run_conv(rm, oracle, geom, M, (100, 0, 0), z=0, seed=4)
 
 
+@pytest.mark.usefixtures("kernels")
 @pytest.mark.parametrize("geom", [(2, 64, 12, 12, 3, 3, 2, 1), (3, 128, 16, 14, 3, 3, 2, 1), (1, 64, 30, 30, 1, 1, 2, 0),
                                   (2, 256, 14, 14, 3, 3, 2, 1), (2, 64, 9, 9, 3, 3, 3, 0), (40, 64, 4, 4, 1, 1, 2, 0)])
 @pytest.mark.parametrize("M", [64, 90])
@@ -244,6 +251,7 @@ def test_conv_strided_lds_patch_kernel(rm, oracle, geom, M):
     assert run_conv(rm, oracle, geom, M, (35, 60, 5), z=z, relu=True, requant=True, seed=6) == 0
 
 
+@pytest.mark.usefixtures("kernels")
 def test_config1_resnet_layer_full_size(rm, oracle):
     """configs[1] at its benchmark size, every output compared: batch 32, 256->256, 14x14, 3x3 s1 p1
     (GEMM 256 x 2304 x 6272), 60:35:5, ReLU + 4-bit requant."""
@@ -276,6 +284,7 @@ def test_config1_resnet_layer_full_size(rm, oracle):
     p.free()
 
 
+@pytest.mark.usefixtures("kernels")
 @pytest.mark.parametrize("geom", [(2, 6, 9, 9, 3, 3, 1, 1), (1, 10, 8, 8, 5, 5, 2, 2), (2, 24, 5, 5, 3, 3, 1, 1)])
 def test_conv_materialised_im2col_fallback(rm, oracle, geom):
     ws = run_conv(rm, oracle, geom, 40, (35, 60, 5), z=3, relu=True, requant=True)
@@ -344,6 +353,7 @@ def test_chained_layers_through_grouped_order(rm, oracle):
     p2.free()
 
 
+@pytest.mark.usefixtures("kernels")
 def test_chained_convolutions_through_grouped_order(rm, oracle):
     """Three 3x3 layers and a shortcut projection chained on the GPU: every layer reads the 4-bit
     tensor the layer before it wrote (grouped row order; its weights are packed with in_perm = that
