@@ -181,19 +181,17 @@ rmsmp_status rmsmp_pack_weights_opt(const float* W, int64_t M, int64_t K, const 
     p->dev.class_tiles[t.kind] += 1;
     p->dev.class_rows[t.kind] += t.nvalid;
   }
-  p->dev.fp6_taps = h.taps;
-  p->dev.fp6_k = (int32_t)h.K;
   if (e == hipSuccess && up.n_fp6) {
     uint8_t* const fp6 = base + up.n_blob + up.n_tables;
     uint32_t* const bound = up.n_bound ? (uint32_t*)(fp6 + up.n_fp6) : nullptr;
     const size_t rows = h.tiles.size() * rmsmp::TILE_M;
     if (bound) e = hipMemsetAsync(bound, 0, rows * 4, nullptr);
-    if (e == hipSuccess) e = (hipError_t)rmsmp::fp6_pack(h, &p->dev, fp6, bound, nullptr);
+    if (e == hipSuccess) e = (hipError_t)rmsmp::fp6_pack(h, p->dev, fp6, bound, &p->fp6, nullptr);
     if (bound) {
       std::vector<uint32_t> sums(rows);
       if (e == hipSuccess) e = hipMemcpy(sums.data(), bound, rows * 4, hipMemcpyDeviceToHost);
       for (uint32_t v : sums)
-        if ((uint64_t)v * 15 >= ((uint64_t)1 << 24)) p->dev.fp6 = nullptr;
+        if ((uint64_t)v * 15 >= ((uint64_t)1 << 24)) p->fp6.w = nullptr;
     } else if (e == hipSuccess) {
       e = hipStreamSynchronize(nullptr);  // the first call may come on any stream
     }
@@ -281,8 +279,9 @@ rmsmp_status rmsmp_gemm(const rmsmp_packed* Wp, const void* X, int64_t N, const 
   if (ep->act_bits == 4 && (Wp->host.K & 1)) return fail(RMSMP_ESHAPE, "gemm: 4-bit activations need an even K");
   if (((uintptr_t)X & 15) != 0) return fail(RMSMP_EINVAL, "gemm: X must be 16-byte aligned");
   if (N > (int64_t)0x7fffffff * 64) return fail(RMSMP_ESHAPE, "gemm: N too large");
-  rmsmp::GemmArgs a;
+  rmsmp::GemmCall a;
   a.w = Wp->dev;
+  a.fp6 = Wp->fp6;
   a.M = Wp->host.M;
   a.K = Wp->host.K;
   a.N = N;
@@ -392,8 +391,9 @@ rmsmp_status rmsmp_conv2d(const rmsmp_packed* Wp, const void* X, const rmsmp_con
   if (!X || !Y) return fail(RMSMP_EINVAL, "conv2d: NULL X or Y");
   if (((uintptr_t)X & 15) != 0) return fail(RMSMP_EINVAL, "conv2d: X must be 16-byte aligned");
   const int64_t N = (int64_t)d->B * OH * OW;
-  rmsmp::GemmArgs a;
+  rmsmp::GemmCall a;
   a.w = Wp->dev;
+  a.fp6 = Wp->fp6;
   a.M = Wp->host.M;
   a.N = N;
   a.Y = Y;
@@ -461,7 +461,7 @@ rmsmp_status rmsmp_conv2d_pair(const rmsmp_packed* WpA, const rmsmp_conv_desc* d
   const rmsmp_conv_desc* d[2] = {dA, dB};
   const rmsmp_epilogue* ep[2] = {epA, epB};
   void* Y[2] = {YA, YB};
-  rmsmp::GemmArgs a[2];
+  rmsmp::GemmCall a[2];
   for (int i = 0; i < 2; ++i) {
     rmsmp_status st = check_epilogue(ep[i], Wp[i]->host.M);
     if (st != RMSMP_OK) return st;
@@ -473,6 +473,7 @@ rmsmp_status rmsmp_conv2d_pair(const rmsmp_packed* WpA, const rmsmp_conv_desc* d
     if (!conv_is_implicit(Wp[i], d[i], ep[i]->act_bits))
       return fail(RMSMP_EWORKSPACE, "conv2d_pair: a layer that needs an im2col workspace cannot be part of a pair; use rmsmp_conv2d");
     a[i].w = Wp[i]->dev;
+    a[i].fp6 = Wp[i]->fp6;
     a[i].M = Wp[i]->host.M;
     a[i].K = Wp[i]->host.K;
     a[i].N = (int64_t)d[i]->B * OH * OW;

@@ -341,7 +341,7 @@ DispatchRecord& last_dispatch() {
   return rec;
 }
 
-int launch_gemm(const GemmArgs& a, void* stream) {
+int launch_gemm(const GemmCall& a, void* stream) {
   hipStream_t s = (hipStream_t)stream;
   last_dispatch() = DispatchRecord{};
   if (a.N <= 0) return 0;

@@ -249,7 +249,7 @@ int try_launch_wide(const GemmArgs& a, void* stream, bool* applied) {
 // layer with the same 64, 128 or 256 input channels, both with 4-bit activations, neither with
 // the GELU epilogue, each fitting the split the pair kernel is built with.  *applied says whether
 // the launch happened; if not, the caller launches the layers one after the other.
-int try_launch_wide_pair(const GemmArgs& a0, const GemmArgs& b0, void* stream, bool* applied) {
+int try_launch_wide_pair(const GemmCall& a0, const GemmCall& b0, void* stream, bool* applied) {
   *applied = false;
   GemmArgs a, b;
   int cca = 0, ccb = 0;
@@ -260,7 +260,7 @@ int try_launch_wide_pair(const GemmArgs& a0, const GemmArgs& b0, void* stream, b
   if (a.d.C != b.d.C || cca != a.d.C || ccb != b.d.C) return 0;
   const int cpt = a.d.C / KSTEP;
   if (cpt != 2 && cpt != 4 && cpt != 8) return 0;
-  if (const int rc = try_launch_fp6_pair(a, b, stream, applied); rc != 0 || *applied) return rc;
+  if (const int rc = try_launch_fp6_pair(a0, b0, stream, applied); rc != 0 || *applied) return rc;
   const WidePairSplit sp = wide_pair_split(cpt);
   if ((a.w.n_tiles + 1) / 2 < sp.ma || (b.w.n_tiles + 1) / 2 < sp.mb) return 0;
   WidePlan pa, pb;

@@ -107,13 +107,17 @@ struct DevicePacked {
   // without touching memory.
   int32_t class_tiles[3] = {0, 0, 0};
   int32_t class_rows[3] = {0, 0, 0};
-  // The weights in 6-bit operand form (fp6_gemm.h); null where a row could exceed what fp32 sums hold.
-  const uint8_t* fp6 = nullptr;
-  int32_t fp6_cb = 0;      // 32-channel blocks per filter tap
-  int32_t fp6_steps = 0;   // 64-deep K steps
-  int32_t fp6_single = 0;  // tiles stored in one part; the others, with Fixed-8 rows, in two
-  int32_t fp6_taps = 1;
-  int32_t fp6_k = 0;       // the layer's K: taps * channels, without padding
+};
+
+// The weights in 6-bit operand form (fp6_gemm.h).  Not part of DevicePacked, which travels in the argument blocks of
+// the int8 kernels: 32 bytes more of those made the 3x3 kernel for 256 channels take 10.62 instead of 10.50 us at batch 64.
+struct Fp6Packed {
+  const uint8_t* w = nullptr;  // null where a row could exceed what fp32 sums hold
+  int32_t cb = 0;      // 32-channel blocks per filter tap
+  int32_t steps = 0;   // 64-deep K steps
+  int32_t single = 0;  // tiles stored in one part; the others, with Fixed-8 rows, in two
+  int32_t taps = 1;
+  int32_t k = 0;       // the layer's K: taps * channels, without padding
 };
 
 // Where weight tile mt lives, computed from DevicePacked alone.
@@ -147,6 +151,11 @@ struct GemmArgs {
   int32_t OH = 0, OW = 0;
   // out_kind 3 only; kept last so that the other epilogues never fetch it
   GeluTable gelu{};
+};
+
+// A call on its way to a kernel: the kernels' arguments, and what only the host and the FP6 kernels need.
+struct GemmCall : GemmArgs {
+  Fp6Packed fp6;
 };
 
 struct Im2colArgs {
@@ -201,18 +210,18 @@ inline bool forced_general() { return forced_split()[0] == 0 && forced_split()[2
 DispatchRecord& last_dispatch();
 
 // Kernel launchers (kernels.hip).  Return hipError_t as int.
-int launch_gemm(const GemmArgs& a, void* stream);
+int launch_gemm(const GemmCall& a, void* stream);
 // LDS-resident implicit-im2col kernel (patch_wide.hip): launches when the layer fits it and says
 // so in *applied.
 int try_launch_wide(const GemmArgs& a, void* stream, bool* applied);
 // Whether it would, and its estimate of the time.
 bool wide_estimate(const GemmArgs& a, float* us);
 // The same kernel for two layers that read one input (a 3x3 and a 1x1 layer), as one launch.
-int try_launch_wide_pair(const GemmArgs& a, const GemmArgs& b, void* stream, bool* applied);
+int try_launch_wide_pair(const GemmCall& a, const GemmCall& b, void* stream, bool* applied);
 // FP6 tile kernel (fp6_gemm.hip); same convention.
-int try_launch_fp6(const GemmArgs& a, void* stream, bool* applied);
+int try_launch_fp6(const GemmCall& a, void* stream, bool* applied);
 // Two convolutions that are small enough for it, as one launch of the split kernel.
-int try_launch_fp6_pair(const GemmArgs& a, const GemmArgs& b, void* stream, bool* applied);
+int try_launch_fp6_pair(const GemmCall& a, const GemmCall& b, void* stream, bool* applied);
 // Skinny kernel (skinny.hip).
 int try_launch_skinny(const GemmArgs& a, void* stream, bool* applied);
 // Split kernel on int8 instructions (i8_split.hip).
@@ -221,7 +230,7 @@ int try_launch_i8_split(const GemmArgs& a, void* stream, bool* applied);
 // them from the packed blob.  Where fp6_needs_bound, bound[padded row] += 1/15 of the row's largest partial sum.
 size_t fp6_weight_bytes(const HostPacked& h);
 bool fp6_needs_bound(const HostPacked& h);
-int fp6_pack(const HostPacked& h, DevicePacked* dev, uint8_t* fp6, uint32_t* bound, void* stream);
+int fp6_pack(const HostPacked& h, const DevicePacked& dev, uint8_t* w, uint32_t* bound, Fp6Packed* out, void* stream);
 // First-layer kernel (conv_first.hip): 3 input channels, 8-bit activations, stride 2; same convention.
 int try_launch_conv_first(const GemmArgs& a, void* stream, bool* applied);
 int launch_im2col(const Im2colArgs& a, void* stream);
@@ -238,6 +247,7 @@ int allow_large_lds(const void* kernel, std::atomic<uint64_t>& done);
 struct rmsmp_packed {
   rmsmp::HostPacked host;
   rmsmp::DevicePacked dev;
+  rmsmp::Fp6Packed fp6;
   void* dev_alloc = nullptr;  // one allocation holding every device table
   size_t dev_bytes = 0;
   int device = 0;
