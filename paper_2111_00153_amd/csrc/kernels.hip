@@ -370,12 +370,7 @@ int launch_gemm(const GemmCall& a, void* stream) {
   }
   {
     bool applied = false;
-    const int rc = try_launch_fp6(a, stream, &applied);
-    if (applied) return rc;
-  }
-  if (!general_only) {
-    bool applied = false;
-    const int rc = try_launch_wide(a, stream, &applied);
+    const int rc = try_launch_tiled(a, stream, &applied);
     if (applied) return rc;
   }
   last_dispatch().kernel = DK_GENERAL;

@@ -2,6 +2,7 @@
 // work-group are shared out, and the dispatch to the per-family launchers (patch_wide_inst.hip).
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 
 #include "patch_wide.h"
@@ -150,7 +151,7 @@ static bool wide_layer_fits(const GemmArgs& a0, GemmArgs* a_out, int* cc_out) {
   return true;
 }
 
-static bool wide_kernel_applies(const GemmArgs& a0, WidePlan* plan, double* cycles = nullptr) {
+static bool wide_kernel_applies(const GemmArgs& a0, WidePlan* plan) {
   GemmArgs a;
   int cc = 0;
   if (!wide_layer_fits(a0, &a, &cc)) return false;
@@ -202,16 +203,34 @@ static bool wide_kernel_applies(const GemmArgs& a0, WidePlan* plan, double* cycl
   }
   if (!have) return false;
   *plan = best;
-  if (cycles) *cycles = best_cost;
   return true;
 }
 
-bool wide_estimate(const GemmArgs& a, float* us) {
-  WidePlan plan;
-  double cycles = 0;
-  if (!wide_kernel_applies(a, &plan, &cycles)) return false;
-  *us = (float)(2.5 + cycles / 2100.0);  // (what a launch costs outside the kernel's own code; the clock under load)
-  return true;
+// What a plan takes in us, for the choice against the FP6 kernels (fp6_gemm.hip says what it was fitted to): unlike the
+// cycles above, which only rank the splits of one call, with the output kind, the class mix and the XCDs.
+static float wide_us(const WidePlan& p) {
+  const GemmArgs& a = p.a;
+  const int taps = a.d.KH * a.d.KW;
+  const bool x4 = p.xb == 4, nine = taps == 9;
+  const float mfmas = (float)taps * p.cpt * p.g.nchunk / p.ks * 2 * p.xb;
+  const float lut = std::min(1.0f, 2.0f * a.w.class_tiles[TILE_NIB_LUT] / a.w.n_tiles);  // tile pairs with a table decode
+  const float kloop = mfmas * (x4 ? (nine ? 0.0167f : 0.02f) : (nine ? 0.0166f : 0.0173f) * (1.0f + 0.79f * lut));
+  const float stage = 1.2e-5f * p.g.patch_rows * p.g.row_stride;
+  const bool out32 = a.ep.out_kind <= 1, unaligned = !out32 && a.M % 16 != 0, bias = a.ep.out_kind == 2 && a.ep.bias;
+  const float block = 0.556f + (out32 ? 1.03f : 0.0f) + (a.ep.out_kind == 3 ? 1.32f : 0.0f) + (unaligned ? 0.56f : 0.0f) + (bias ? 0.216f : 0.0f);
+  const float group = stage + kloop + (p.g.nchunk - 1) * (0.46f + stage) + 3.3e-5f * pw_xch_bytes(p.xb, p.ks, p.ks * p.nwt * p.ms) + 2.0f * p.xb / p.ks * block + (bias ? 0.504f : 0.0f);
+  const float extra = x4 ? mfmas * 0.0227f : mfmas * 0.021f + 0.234f * (group - kloop);  // one more on the same unit
+  const int by_lds = (int)((160 * 1024) / p.lds), by_regs = x4 || p.g.nchunk > 1 ? 2 : 3;
+  const int share = by_lds < by_regs ? by_lds : by_regs;
+  // work-groups per compute unit: the column blocks are dealt out to the eight XCDs; tile pairs that a work-group
+  // has no work for cost nothing
+  const float per_unit = (float)((p.g.gx + 7) / 8) * ((a.w.n_tiles + 1) / 2) / p.ms / 32.0f;
+  const float n = per_unit < 1.0f ? 1.0f : std::ceil(per_unit - (share > 1 ? 0.15f : 0.0f));
+  const float full = std::floor(n / share), rest = n - full * share, round = group + (share - 1) * extra;
+  float time = full * round + (rest > 0.0f ? group + (rest - 1.0f) * extra : 0.0f);
+  if (per_unit > share) time = 0.806f * time + 0.194f * per_unit / share * round;
+  const float megabytes = (float)((double)a.M * a.N * 4e-6);
+  return 2.23f + time + (out32 ? (a.N % 32 == 0 ? 0.135f : 0.153f) * megabytes : 0.0f) + (unaligned ? 0.17f * megabytes : 0.0f);
 }
 
 static int launch_wide(const WidePlan& p, hipStream_t s) {
@@ -231,10 +250,11 @@ static int launch_wide(const WidePlan& p, hipStream_t s) {
   return (int)hipErrorInvalidValue;
 }
 
-// Launches the wide kernel when the layer fits it; *applied says whether it did.
-int try_launch_wide(const GemmArgs& a, void* stream, bool* applied) {
+// Launches the wide kernel when the layer fits it and it is estimated to take less than limit_us; *applied says
+// whether it did.
+int try_launch_wide(const GemmArgs& a, void* stream, float limit_us, bool* applied) {
   WidePlan plan;
-  *applied = wide_kernel_applies(a, &plan);
+  *applied = wide_kernel_applies(a, &plan) && (std::isinf(limit_us) || wide_us(plan) < limit_us);
   const int* forced = forced_split();
   if (*applied && forced[0] > 0) {
     WidePlan p2;
@@ -260,12 +280,12 @@ int try_launch_wide_pair(const GemmCall& a0, const GemmCall& b0, void* stream, b
   if (a.d.C != b.d.C || cca != a.d.C || ccb != b.d.C) return 0;
   const int cpt = a.d.C / KSTEP;
   if (cpt != 2 && cpt != 4 && cpt != 8) return 0;
-  if (const int rc = try_launch_fp6_pair(a0, b0, stream, applied); rc != 0 || *applied) return rc;
   const WidePairSplit sp = wide_pair_split(cpt);
-  if ((a.w.n_tiles + 1) / 2 < sp.ma || (b.w.n_tiles + 1) / 2 < sp.mb) return 0;
   WidePlan pa, pb;
-  if (!wide_plan_mode(a, cca, sp.xa, sp.ka, sp.na, sp.ma, &pa) || !wide_plan_mode(b, ccb, sp.xb, sp.kb, sp.nb, sp.mb, &pb)) return 0;
-  if ((uint64_t)pa.blocks + pb.blocks > 0x7fffffffu) return 0;
+  const bool fits = (a.w.n_tiles + 1) / 2 >= sp.ma && (b.w.n_tiles + 1) / 2 >= sp.mb && wide_plan_mode(a, cca, sp.xa, sp.ka, sp.na, sp.ma, &pa) &&
+                    wide_plan_mode(b, ccb, sp.xb, sp.kb, sp.nb, sp.mb, &pb) && (uint64_t)pa.blocks + pb.blocks <= 0x7fffffffu;
+  if (const int rc = try_launch_fp6_pair(a0, b0, fits, stream, applied); rc != 0 || *applied) return rc;
+  if (!fits) return 0;
   *applied = true;
   last_dispatch() = DispatchRecord{DK_LDS_RESIDENT_PAIR};
 #define RMSMP_WIDE_CASE(CP) \

@@ -212,16 +212,17 @@ DispatchRecord& last_dispatch();
 // Kernel launchers (kernels.hip).  Return hipError_t as int.
 int launch_gemm(const GemmCall& a, void* stream);
 // LDS-resident implicit-im2col kernel (patch_wide.hip): launches when the layer fits it and says
-// so in *applied.
-int try_launch_wide(const GemmArgs& a, void* stream, bool* applied);
-// Whether it would, and its estimate of the time.
-bool wide_estimate(const GemmArgs& a, float* us);
+// so in *applied.  limit_us: only if it is estimated to take less.
+int try_launch_wide(const GemmArgs& a, void* stream, float limit_us, bool* applied);
 // The same kernel for two layers that read one input (a 3x3 and a 1x1 layer), as one launch.
 int try_launch_wide_pair(const GemmCall& a, const GemmCall& b, void* stream, bool* applied);
-// FP6 tile kernel (fp6_gemm.hip); same convention.
+// FP6 kernels (fp6_gemm.hip); same convention.
 int try_launch_fp6(const GemmCall& a, void* stream, bool* applied);
-// Two convolutions that are small enough for it, as one launch of the split kernel.
-int try_launch_fp6_pair(const GemmCall& a, const GemmCall& b, void* stream, bool* applied);
+// Those or the LDS-resident kernel, whichever is estimated to be faster.
+int try_launch_tiled(const GemmCall& a, void* stream, bool* applied);
+// Two convolutions that are small enough for it, as one launch of the FP6 split kernel.  int8_pair: whether the LDS-resident
+// kernel would take both as one launch.
+int try_launch_fp6_pair(const GemmCall& a, const GemmCall& b, bool int8_pair, void* stream, bool* applied);
 // Skinny kernel (skinny.hip).
 int try_launch_skinny(const GemmArgs& a, void* stream, bool* applied);
 // Split kernel on int8 instructions (i8_split.hip).

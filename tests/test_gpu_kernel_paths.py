@@ -275,6 +275,34 @@ def test_dispatch_record_names_the_kernel(rm, oracle, only, M, K, N, bits, reque
     p.free()
 
 
+# calls where one family of kernels is ahead by 7 % and more in measurements, each of them once given to the other one:
+# few columns on deep K, 4-bit and fp32 output of one GEMM, strided 1x1 layers over many pixels
+CHOICES = [((4096, 4096, 300), "u4", "lds_resident"), ((3072, 768, 4096), "fp32", "fp6_tile"), ((4096, 4096, 100), "fp32", "fp6_split"),
+           ((64, 128, 64, 56), "u4", "lds_resident"), ((128, 256, 64, 28), "u4", "lds_resident"), ((256, 512, 64, 14), "u4", "lds_resident"),
+           ((64, 128, 1, 56), "u4", "fp6_split"), ((256, 512, 2, 14), "u4", "fp6_split")]
+
+
+@pytest.mark.parametrize("sizes,out,want", CHOICES)
+def test_the_faster_family_of_kernels_is_chosen(rm, sizes, out, want):
+    """(M, K, N): a GEMM; (C, M, B, side): a 1x1 layer of stride 2."""
+    rng = np.random.default_rng(8)
+    gemm = len(sizes) == 3
+    M, K = (sizes[0], sizes[1]) if gemm else (sizes[1], sizes[0])
+    scheme = si.scheme_permutation(rng, rm.rmsmp_ratio_counts(M, 35, 60, 5))
+    p = rm.rmsmp_pack_weights(si.weights_rowscaled(rng, M, K), scheme)
+    N = sizes[2] if gemm else sizes[2] * (sizes[3] // 2) ** 2
+    Y = torch.empty((N, M // 2), dtype=torch.uint8, device=DEV) if out == "u4" else torch.empty((M, N), dtype=torch.float32, device=DEV)
+    ep = rm.make_epilogue(0.05, 0, 4, None, out == "u4", rm.OUT_U4 if out == "u4" else rm.OUT_FP32, 0.3)
+    if gemm:
+        rm.rmsmp_gemm(p, torch.zeros((N, K // 2), dtype=torch.uint8, device=DEV), N, ep, Y)
+    else:
+        d = rm.ConvDesc(sizes[2], K, sizes[3], sizes[3], 1, 1, 2, 0)
+        rm.rmsmp_conv2d(p, torch.zeros((sizes[2], sizes[3], sizes[3], K // 2), dtype=torch.uint8, device=DEV), d, ep, Y)
+    assert rm.rmsmp_debug_last_dispatch()[0] == want
+    torch.cuda.synchronize()
+    p.free()
+
+
 def test_dispatch_record_of_convolutions(rm, only):
     """Convolutions that are read where they lie whatever their width, and pairs, write the whole record: nothing of an
     earlier launch stays in it."""
