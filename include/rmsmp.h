@@ -82,7 +82,8 @@ rmsmp_status rmsmp_assign_by_variance(const float* W, int64_t M, int64_t K, int6
  *   PoT-4   (Eq. 3-4): level 0 or +-alpha*2^-k, k = 0..6, k = -round(log2 |clip(w/alpha)|),
  *                      zero iff |clip| <= 2^-7;  rounding is half-to-even, all in fp32.
  * Rows are grouped by scheme, 4-bit codes are nibble-packed, and the blob is copied to
- * the current device (synchronously).  On success *out owns the device memory; release
+ * the current device (synchronously), where it is also written in the form the matrix
+ * instructions read (see RMSMP_PACK_NO_OPERAND_FORM).  On success *out owns the device memory; release
  * it with rmsmp_free_packed.  Errors: EINVAL (NULL, bad scheme code, alpha <= 0),
  * ESHAPE (M, K < 1, K % taps), ENOMEM, EHIP.
  */
@@ -99,9 +100,19 @@ rmsmp_status rmsmp_pack_weights(const float* W, int64_t M, int64_t K, const uint
  *       costs (the opposite of Section 4's FPGA, where PoT rows are the cheap ones), so this
  *       pays for compute-bound layers -- convolutions, GEMMs with many columns -- and costs
  *       bandwidth where the weights are the traffic (N <= 64).
+ *   RMSMP_PACK_NO_OPERAND_FORM  only the packed blob is kept on the device.  Without this flag a
+ *       layer is stored a second time as operands of the 6-bit matrix instructions, which calls
+ *       with 4-bit activations and more than 64 columns run on where they are the faster way: 0.75
+ *       bytes per weight, 1.5 in blocks of 32 rows that hold Fixed-8 rows (or PoT-4 rows stored as
+ *       int8 beside them), beside 0.5 and 1 byte in the blob; a 4096 x 4096 layer at 40:50:10 takes
+ *       23 MB instead of 9.2.  Results are the same bit for bit.  The flag is for layers that never see
+ *       such calls (8-bit activations, token-by-token serving), and for programs short of memory.
+ *       The second form is left out by itself for layers with at most 4 input channels, where a row
+ *       could exceed what its fp32 sums hold exactly, and where the device has no memory left for it.
  * Errors: as rmsmp_pack_weights, plus EINVAL for an unknown flag.
  */
 #define RMSMP_PACK_POT_AS_INT8 1u
+#define RMSMP_PACK_NO_OPERAND_FORM 4u
 rmsmp_status rmsmp_pack_weights_opt(const float* W, int64_t M, int64_t K, const uint8_t* scheme,
                                     const float* alpha, int32_t taps, const int32_t* in_perm,
                                     uint32_t flags, rmsmp_packed** out);

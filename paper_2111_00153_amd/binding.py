@@ -166,6 +166,7 @@ class Packed:
 
 
 PACK_POT_AS_INT8 = 1  # RMSMP_PACK_POT_AS_INT8
+PACK_NO_OPERAND_FORM = 4  # RMSMP_PACK_NO_OPERAND_FORM
 
 
 def rmsmp_pack_weights(W, scheme, alpha=None, taps=1, in_perm=None, flags=0):

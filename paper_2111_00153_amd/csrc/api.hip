@@ -109,25 +109,40 @@ rmsmp_status rmsmp_pack_weights(const float* W, int64_t M, int64_t K, const uint
 rmsmp_status rmsmp_pack_weights_opt(const float* W, int64_t M, int64_t K, const uint8_t* scheme, const float* alpha,
                                     int32_t taps, const int32_t* in_perm, uint32_t flags, rmsmp_packed** out) {
   if (!out) return fail(RMSMP_EINVAL, "pack_weights: out is NULL");
-  if (flags & ~RMSMP_PACK_POT_AS_INT8) return fail(RMSMP_EINVAL, "pack_weights: unknown flag");
+  if (flags & ~(RMSMP_PACK_POT_AS_INT8 | RMSMP_PACK_NO_OPERAND_FORM)) return fail(RMSMP_EINVAL, "pack_weights: unknown flag");
   *out = nullptr;
   rmsmp_packed* p = new (std::nothrow) rmsmp_packed();
   if (!p) return fail(RMSMP_ENOMEM, "pack_weights: host allocation failed");
-  // one device allocation: blob | tiles, row metadata, lut | weights in 6-bit operand form | row bounds
+  // one device allocation: blob | tiles, row metadata, lut | weights in 6-bit operand form.  Where the rows of that form
+  // have to be looked at before it may be used, it has an allocation of its own (operand form | row bounds), which
+  // goes if a row is beyond the bound.
   struct Upload : rmsmp::PackSink {
     rmsmp_packed* p;
+    bool operand_form = true;
     size_t n_blob = 0, n_tables = 0, n_fp6 = 0, n_bound = 0;
     hipError_t e = hipSuccess;
     bool no_memory = false;
     void begin(const rmsmp::HostPacked& h) override {
       n_blob = align_up(h.blob_bytes, 256);
       n_tables = align_up(h.tiles.size() * sizeof(rmsmp::TileDesc), 256) + align_up(h.p_meta.size() * 4, 256) + align_up(h.p_lut.size() * 4, 256);
-      n_fp6 = align_up(rmsmp::fp6_weight_bytes(h), 256);
+      n_fp6 = operand_form ? align_up(rmsmp::fp6_weight_bytes(h), 256) : 0;
       n_bound = n_fp6 && rmsmp::fp6_needs_bound(h) ? align_up(h.tiles.size() * rmsmp::TILE_M * 4, 256) : 0;
-      p->dev_bytes = n_blob + n_tables + n_fp6 + n_bound;
+      p->dev_bytes = n_blob + n_tables + (n_bound ? 0 : n_fp6);
       e = hipGetDevice(&p->device);
       if (e != hipSuccess) return;
-      e = hipMalloc(&p->dev_alloc, p->dev_bytes);
+      auto alloc = [](void** at, size_t bytes) {
+        const hipError_t rc = hipMalloc(at, bytes);
+        if (rc != hipSuccess) *at = nullptr;
+        return rc;
+      };
+      e = alloc(&p->dev_alloc, p->dev_bytes);
+      if (e == hipSuccess && n_bound) e = alloc(&p->fp6_alloc, n_fp6 + n_bound);
+      if (e != hipSuccess && n_fp6) {  // short of memory: a layer works without the operand form
+        (void)hipGetLastError();
+        n_fp6 = n_bound = 0;
+        p->dev_bytes = n_blob + n_tables;
+        e = p->dev_alloc ? hipSuccess : alloc(&p->dev_alloc, p->dev_bytes);
+      }
       no_memory = e != hipSuccess;
     }
     void take(const uint8_t* blob, size_t off, size_t bytes) override {
@@ -135,10 +150,8 @@ rmsmp_status rmsmp_pack_weights_opt(const float* W, int64_t M, int64_t K, const 
     }
   } up;
   up.p = p;
-  auto drop = [&]() {
-    if (p->dev_alloc) (void)hipFree(p->dev_alloc);
-    delete p;
-  };
+  up.operand_form = !(flags & RMSMP_PACK_NO_OPERAND_FORM);
+  auto drop = [&]() { rmsmp_free_packed(p); };
   std::string err;
   rmsmp_status st;
   try {
@@ -182,7 +195,7 @@ rmsmp_status rmsmp_pack_weights_opt(const float* W, int64_t M, int64_t K, const 
     p->dev.class_rows[t.kind] += t.nvalid;
   }
   if (e == hipSuccess && up.n_fp6) {
-    uint8_t* const fp6 = base + up.n_blob + up.n_tables;
+    uint8_t* const fp6 = up.n_bound ? (uint8_t*)p->fp6_alloc : base + up.n_blob + up.n_tables;
     uint32_t* const bound = up.n_bound ? (uint32_t*)(fp6 + up.n_fp6) : nullptr;
     const size_t rows = h.tiles.size() * rmsmp::TILE_M;
     if (bound) e = hipMemsetAsync(bound, 0, rows * 4, nullptr);
@@ -192,6 +205,10 @@ rmsmp_status rmsmp_pack_weights_opt(const float* W, int64_t M, int64_t K, const 
       if (e == hipSuccess) e = hipMemcpy(sums.data(), bound, rows * 4, hipMemcpyDeviceToHost);
       for (uint32_t v : sums)
         if ((uint64_t)v * 15 >= ((uint64_t)1 << 24)) p->fp6.w = nullptr;
+      if (e == hipSuccess && !p->fp6.w) {
+        e = hipFree(p->fp6_alloc);
+        p->fp6_alloc = nullptr;
+      }
     } else if (e == hipSuccess) {
       e = hipStreamSynchronize(nullptr);  // the first call may come on any stream
     }
@@ -231,6 +248,7 @@ rmsmp_status rmsmp_pack_roundtrip_host(const float* W, int64_t M, int64_t K, con
 void rmsmp_free_packed(rmsmp_packed* p) {
   if (!p) return;
   if (p->dev_alloc) (void)hipFree(p->dev_alloc);
+  if (p->fp6_alloc) (void)hipFree(p->fp6_alloc);
   delete p;
 }
 

@@ -250,6 +250,7 @@ struct rmsmp_packed {
   rmsmp::DevicePacked dev;
   rmsmp::Fp6Packed fp6;
   void* dev_alloc = nullptr;  // one allocation holding every device table
-  size_t dev_bytes = 0;
+  void* fp6_alloc = nullptr;  // the operand form of layers whose rows had to be checked first
+  size_t dev_bytes = 0;       // of dev_alloc
   int device = 0;
 };

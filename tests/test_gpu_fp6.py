@@ -182,6 +182,51 @@ def test_a_bias_that_is_no_number_gives_code_15(rm, N):
     p.free()
 
 
+def _pack_and_bytes(rm, W, scheme, flags):
+    """The packed layer and the device memory it took."""
+    torch.cuda.synchronize()
+    before = torch.cuda.mem_get_info()[0]
+    p = rm.rmsmp_pack_weights(W, scheme, flags=flags)
+    torch.cuda.synchronize()
+    return p, before - torch.cuda.mem_get_info()[0]
+
+
+# a layer with all row classes whose rows are below the bound by their K, and one whose rows are beyond it
+@pytest.mark.parametrize("M,K,beyond", [(4096, 2048, False), (2048, 17536, True)])
+def test_device_memory_of_the_operand_form(rm, oracle, M, K, beyond):
+    """The second copy of the weights is kept where calls can use it and the caller wants it, and nowhere else; the
+    results do not depend on it."""
+    N = 70
+    rng = np.random.default_rng(9)
+    slack = 8 << 20  # what an allocation may be rounded up by, and tables
+    if beyond:
+        W, scheme = np.full((M, K), 0.5, np.float32), np.ones(M, np.uint8)
+        x = np.full((N, K), 15, np.uint8)
+        x[3, :5] = 0
+        blob, operand = M * K // 2, M * K * 3 // 4
+    else:
+        W, scheme = si.weights_rowscaled(rng, M, K), si.scheme_permutation(rng, rm.rmsmp_ratio_counts(M, 40, 50, 10))
+        x = si.act_codes_u4(rng, (N, K))
+        blob, operand = M * K * 55 // 100, M * K * 3 // 4 * 11 // 10
+    rows = slice(0, M, 97)
+    ref = oracle.quantize_rows(W[rows], scheme[rows])
+    acc = oracle.gemm_acc(ref["wint"], x.astype(np.int32))
+    X = _to_dev(rm.pack_u4(x))
+    for flags in (0, rm.PACK_NO_OPERAND_FORM):
+        p, took = _pack_and_bytes(rm, W, scheme, flags)
+        want = blob + (operand if flags == 0 and not beyond else 0)
+        assert want * 0.95 - slack // 4 <= took <= want * 1.05 + slack, (took, want)
+        Y = torch.full((M, N), -777, dtype=torch.int32, device=DEV)
+        rm.rmsmp_gemm(p, X, N, rm.make_epilogue(0.05, 0, 4, None, False, rm.OUT_INT32), Y)
+        kernel = rm.rmsmp_debug_last_dispatch()[0]
+        assert (kernel in ("fp6_split", "fp6_tile")) == (flags == 0 and not beyond), kernel
+        torch.cuda.synchronize()
+        assert np.array_equal(Y[rows].cpu().numpy(), acc)
+        p.free()
+    p = rm.rmsmp_pack_weights(W[:64], scheme[:64], flags=rm.PACK_NO_OPERAND_FORM | rm.PACK_POT_AS_INT8)
+    p.free()
+
+
 @pytest.mark.parametrize("scheme_code,K", [(1, 17536), (2, 8832), (1, 17472), (2, 8768)])
 def test_rows_beyond_what_fp32_sums_hold_use_the_int8_kernels(rm, oracle, scheme_code, K):
     """Every weight at its row's maximum and every code 15: from a K on the sums pass 2^24 and the layer must not run
