@@ -45,11 +45,14 @@ def test_fake_quant_rows_matches_oracle_bitwise(rm, oracle, M, K, with_alpha):
 
 # the largest and smallest rows of each way a row is held, 16-byte aligned and not, and scaling factors at and beyond the
 # ends of the range in which the quotient is corrected instead of divided
-@pytest.mark.parametrize("K", [1, 64, 65, 255, 256, 257, 1024, 1025, 1028, 2048, 2049, 4096, 4100, 8191, 8192, 8193, 32768, 32772])
-@pytest.mark.parametrize("M", [3, 1026])
+# (the backward of rows that are no multiple of 16 bytes reads them 16 bytes at a time from 2^22 elements on: short rows, of which
+# a work-group has many, rows of 2^k + 1 and 2^k - 1, a last read that ends with the tensor and one that does not)
+ROWS = ([(M, K) for M in (3, 1026) for K in (1, 64, 65, 255, 256, 257, 1024, 1025, 1028, 2048, 2049, 4096, 4100, 8191, 8192, 8193)] +
+        [(3, 32768), (3, 32772), (1024, 8196), (1026, 12292), (1024, 16384), (1024, 16388), (32515, 129), (8209, 513), (4099, 1023), (16383, 257), (129, 32771)])
+
+
+@pytest.mark.parametrize("M,K", ROWS)
 def test_projection_and_its_backward_at_every_row_length(rm, oracle, M, K):
-    if M * K > 1 << 23:
-        pytest.skip("the oracle takes too long")
     rng = np.random.default_rng(M + K)
     W = si.weights_rowscaled(rng, M, K)
     W[0] *= np.float32(2.0 ** 64)
