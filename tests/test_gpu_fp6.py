@@ -26,15 +26,15 @@ def _to_dev(a):
     return torch.from_numpy(np.ascontiguousarray(a)).to(DEV)
 
 
-def _check_outputs(rm, oracle, call, p, M, N, ref, acc, z, bias, relu):
+def _check_outputs(rm, oracle, call, p, M, N, ref, acc, z, bias, relu, bits=4):
     """int32, fp32, 4-bit and GELU outputs of call(Y, epilogue) against the oracle's epilogue of acc."""
     rs = oracle.rowsum(ref["wint"])
     bias_d = None if bias is None else _to_dev(bias)
     acc_c, y, _ = oracle.epilogue(acc, rs, z, ref["rowscale"], 0.05, bias, relu)
     Y = torch.full((M, N), -777, dtype=torch.int32, device=DEV)
-    call(Y, rm.make_epilogue(0.05, z, 4, None, False, rm.OUT_INT32))
+    call(Y, rm.make_epilogue(0.05, z, bits, None, False, rm.OUT_INT32))
     Yf = torch.full((M, N), np.nan, dtype=torch.float32, device=DEV)
-    call(Yf, rm.make_epilogue(0.05, z, 4, bias_d, relu, rm.OUT_FP32))
+    call(Yf, rm.make_epilogue(0.05, z, bits, bias_d, relu, rm.OUT_FP32))
     torch.cuda.synchronize()
     assert np.array_equal(Y.cpu().numpy(), acc_c)
     assert np.all(np.abs(Yf.cpu().numpy() - y) <= 1e-5 * np.abs(y))
@@ -44,7 +44,15 @@ def _check_outputs(rm, oracle, call, p, M, N, ref, acc, z, bias, relu):
     inv = np.float32(15.0 / max(float(np.percentile(pos, 99.0)) if pos.size else 1.0, 1e-6))
     _, _, q = oracle.epilogue(acc, rs, z, ref["rowscale"], 0.05, bias, relu, inv)
     Yq = torch.full((N, M // 2), 0xEE, dtype=torch.uint8, device=DEV)
-    call(Yq, rm.make_epilogue(0.05, z, 4, bias_d, relu, rm.OUT_U4, inv))
+    call(Yq, rm.make_epilogue(0.05, z, bits, bias_d, relu, rm.OUT_U4, inv))
+    torch.cuda.synchronize()
+    got = rm.unpack_u4(Yq.cpu().numpy())
+    assert np.array_equal(got, np.ascontiguousarray(q[p.perm].T))
+    _, y, _ = oracle.epilogue(acc, rs, z, ref["rowscale"], 0.05, bias, False)
+    inv = float(np.float32(14.0 / max(float(np.percentile(np.abs(y), 99.0)), 1e-6)))
+    _, q = oracle.epilogue_gelu(acc, rs, z, ref["rowscale"], 0.05, bias, inv, 1)
+    Yq = torch.full((N, M // 2), 0xEE, dtype=torch.uint8, device=DEV)
+    call(Yq, rm.make_epilogue(0.05, z, bits, bias_d, False, rm.OUT_GELU_U4, inv, 1))
     torch.cuda.synchronize()
     got = rm.unpack_u4(Yq.cpu().numpy())
     assert np.array_equal(got, np.ascontiguousarray(q[p.perm].T))
@@ -164,6 +172,25 @@ def test_skinny_every_work_group_shape(rm, oracle, shape, M, K, N, ratio):
         p.free()
 
 
+# 8-bit activations: the split kernel on int8 instructions with 8 and 16 waves, columns of 16 bytes and not, K steps that the
+# waves do not share evenly, all row classes
+@pytest.mark.parametrize("M,K,N,ratio,waves", [(34, 147, 33, (35, 60, 5), 8), (64, 512, 1, (0, 0, 100), 8), (130, 2050, 40, (60, 35, 5), 16),
+                                               (1000, 512, 64, (0, 0, 100), 8), (70, 4112, 65, (35, 60, 5), 16), (96, 64, 320, (100, 0, 0), 8)])
+def test_int8_split(rm, oracle, M, K, N, ratio, waves):
+    rng = np.random.default_rng(M + K + N)
+    W = si.weights_rowscaled(rng, M, K)
+    scheme = si.scheme_permutation(rng, rm.rmsmp_ratio_counts(M, *ratio))
+    x = si.act_codes_i8(rng, (N, K))
+    bias = rng.normal(0.0, 0.3, M).astype(np.float32)
+    ref = oracle.quantize_rows(W, scheme)
+    acc = oracle.gemm_acc(ref["wint"], x.astype(np.int32))
+    p = rm.rmsmp_pack_weights(W, scheme)
+    X = _to_dev(x)
+    _check_outputs(rm, oracle, lambda Y, ep: rm.rmsmp_gemm(p, X, N, ep, Y), p, M, N, ref, acc, -3, bias, True, 8)
+    assert rm.rmsmp_debug_last_dispatch() == ("int8_split", (waves, 0, 0, 0 if K % 16 == 0 else 2))
+    p.free()
+
+
 @pytest.mark.parametrize("N", [8, 100, 300])
 def test_a_bias_that_is_no_number_gives_code_15(rm, N):
     """Through the skinny, the split and the tile kernel as through the others: the upper clamp is what a NaN ends at."""
@@ -179,6 +206,61 @@ def test_a_bias_that_is_no_number_gives_code_15(rm, N):
         rm.rmsmp_debug_set_wave_split(0, 0, 0, 0)
         torch.cuda.synchronize()
         assert np.all(rm.unpack_u4(Y.cpu().numpy())[:, int(np.flatnonzero(p.perm == 5)[0])] == 15)
+    p.free()
+
+
+@pytest.mark.parametrize("shape", [1, 4, 6, 8, 9])
+@pytest.mark.parametrize("scheme_code", [1, 2])
+def test_mixed_sums_just_below_what_fp32_holds(rm, oracle, scheme_code, shape):
+    """Rows whose weights are as large as a layer of the FP6 kernels may have: 15 times the sum of what the operands
+    hold of a level is just below 2^24.  The largest and the smallest level in one instruction, large sums that small
+    products are added to and large ones taken from, odd sums, both signs: every sum exact."""
+    M, N = 34, 70
+    rng = np.random.default_rng(24 + scheme_code)
+    levels = np.array([0] + [s * 2 ** e for s in (-1, 1) for e in range(7)]) if scheme_code == 1 else np.arange(-127, 128)
+
+    def cost(q):  # of a level q: |q|, or |16 h| + |l| of its two parts
+        h = (q + 8) >> 4
+        return np.abs(q) if scheme_code == 1 else 16 * np.abs(h) + np.abs(q - 16 * h)
+
+    limit = ((1 << 24) - 1) // 15
+    top = int(levels.max())
+    K = 2 * (limit // int(cost(np.array([top, 1])).sum()))
+    Q = np.zeros((M, K), np.int64)
+    Q[0, 0::2], Q[0, 1::2] = top, 1                        # largest and smallest level by turns
+    Q[1, : K // 2], Q[1, K // 2:] = top, 1                 # small products on top of a large sum
+    Q[2, : K // 2], Q[2, K // 2:] = 1, top
+    Q[3, 0::2], Q[3, 1::2] = top, -1
+    Q[4, : K // 2: 2], Q[4, K // 2:: 2] = top, -top        # a large sum, then back to nothing
+    Q[5] = -Q[0]
+    Q[6, : K // 2] = -Q[1, : K // 2]
+    for r in range(7, M):                                  # any levels, as many as the row may have
+        q = rng.choice(levels, K)
+        q[np.cumsum(cost(q)) > limit] = 0
+        Q[r] = rng.permutation(q) if r % 2 else q
+    assert cost(Q).sum(axis=1).max() <= limit and cost(Q[0]).sum() > 0.999 * limit
+    W = (Q / float(top)).astype(np.float32)
+    scheme, alpha = np.full(M, scheme_code, np.uint8), np.ones(M, np.float32)
+    ref = oracle.quantize_rows(W, scheme, alpha=alpha)
+    assert np.array_equal(ref["wint"], Q)
+    x = si.act_codes_u4(rng, (N, K))
+    x[:8] = 15
+    x[4, -1] = 14
+    x[5, ::2] = 1
+    x[6, 1::2] = 1
+    p = rm.rmsmp_pack_weights(W, scheme, alpha=alpha)
+    rm.rmsmp_debug_set_wave_split(0, shape, 0, 0)
+    try:
+        Y = torch.full((M, N), -777, dtype=torch.int32, device=DEV)
+        rm.rmsmp_gemm(p, _to_dev(rm.pack_u4(x)), N, rm.make_epilogue(0.05, 0, 4, None, False, rm.OUT_INT32), Y)
+        assert rm.rmsmp_debug_last_dispatch()[0] == ("fp6_tile" if shape <= 6 else "fp6_split")
+    finally:
+        rm.rmsmp_debug_set_wave_split(0, 0, 0, 0)
+    torch.cuda.synchronize()
+    acc = oracle.gemm_acc(ref["wint"], x.astype(np.int32))
+    # (127 is 128 - 1 in two parts: its sums end 1.5 % below those of the parts)
+    assert int(np.abs(acc).max()) > 0.98 * (1 << 24) and (acc % 2).any()
+    assert np.array_equal(Y.cpu().numpy(), acc)
     p.free()
 
 
