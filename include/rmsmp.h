@@ -339,6 +339,8 @@ rmsmp_status rmsmp_debug_gelu_breakpoints(float out_inv_scale, int32_t out_zero_
  * synchronizes the device: never call it on a hot path.  Errors: EHIP.
  */
 rmsmp_status rmsmp_debug_measure_peaks(double* mfma_int8_tops, double* copy_gbs);
+/* The same for the 6-bit matrix instruction (TOP/s; HOST).  Errors: EINVAL, EHIP. */
+rmsmp_status rmsmp_debug_measure_mfma6(double* mfma6_tops);
 
 #ifdef __cplusplus
 }

@@ -1,7 +1,7 @@
 #!/usr/bin/env python3
 """Times the library on every benchmark configuration (synthetic inputs, one GPU) and prints a table.
 
-    python -m paper_2111_00153_amd.bench_configs [gemm] [conv] [skinny] [sweep] [extra] [qat] [calib]
+    python -m paper_2111_00153_amd.bench_configs [gemm] [conv] [skinny] [sweep] [extra] [qat] [peaks] [cases [NAME ...]] [calib]
 
 (`calib` adds one plain 256 MiB device-to-device copy: a kernel of known size to scale rocprofv3's
 FETCH_SIZE / WRITE_SIZE readings with when the script runs under the profiler.)
@@ -11,7 +11,8 @@ events; the median block is reported.  Throughput counts 2*M*K*N operations of t
 whatever the row schemes or padding.  The skinny configuration (weights 4096 x 4096, 1..64
 activation columns) is timed twice: "warm" launches the same packed weights every time (they stay
 in the last-level cache), "cold" rotates through enough packed copies (> 512 MB) that every launch
-streams its weights from HBM.  No oracle is involved here: parity is the tests' job.
+streams its weights from HBM.  `peaks` prints the machine's own rates, `cases` takes the
+listed cases of perf/cases.py, or those named, through 20 passes each (for a profiler).  No oracle is involved here: parity is the tests' job.
 """
 import os
 import sys
@@ -183,6 +184,21 @@ def main():
         extra_layers()
     if "qat" in which:
         qat_kernels()
+    if "peaks" in which:
+        mfma, copy = rm.rmsmp_debug_measure_peaks()
+        print("MFMA only: int8 %.0f TOP/s, 6-bit %.0f TOP/s; plain copy kernel, 1 GiB: %.0f GB/s (read + written)" % (mfma, rm.rmsmp_debug_measure_mfma6(), copy), flush=True)
+        for mib in (256, 1024):
+            src = torch.zeros(mib << 18, dtype=torch.float32, device="cuda")
+            dst = torch.empty_like(src)
+            us = time_launches([lambda: dst.copy_(src)], iters=20)
+            print("torch copy_, %4d MiB: %.0f GB/s (read + written)" % (mib, 2.0 * (mib << 20) / us / 1e3), flush=True)
+    if "cases" in which:
+        from perf import cases
+        listed = cases.listed()
+        for case in [c for c in listed if c["name"] in which] or listed:
+            state = cases.prepare(case, 1)
+            us = time_launches([lambda: cases.run(state)], iters=4, warm=0)
+            print("case %-14s %9.2f us a pass" % (case["name"], us), flush=True)
     if "calib" in which:
         src = torch.empty(256 << 20, dtype=torch.uint8, device=DEV).fill_(1)
         dst = torch.empty_like(src)

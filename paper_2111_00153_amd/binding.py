@@ -55,7 +55,7 @@ EXPORTS = ["rmsmp_last_error", "rmsmp_version", "rmsmp_ratio_counts", "rmsmp_ass
            "rmsmp_pack_roundtrip_host", "rmsmp_gemm", "rmsmp_conv2d", "rmsmp_conv2d_workspace_size",
            "rmsmp_fake_quant_rows", "rmsmp_ste_backward", "rmsmp_debug_set_wave_split",
            "rmsmp_debug_last_dispatch", "rmsmp_debug_measure_peaks", "rmsmp_init", "rmsmp_conv2d_static_workspace", "rmsmp_debug_gelu_breakpoints",
-           "rmsmp_conv2d_pair", "rmsmp_pack_weights_opt"]
+           "rmsmp_conv2d_pair", "rmsmp_pack_weights_opt", "rmsmp_debug_measure_mfma6"]
 
 
 def _check(rc):
@@ -343,6 +343,13 @@ def rmsmp_debug_measure_peaks():
     a, b = ctypes.c_double(), ctypes.c_double()
     _check(_lib.rmsmp_debug_measure_peaks(ctypes.byref(a), ctypes.byref(b)))
     return float(a.value), float(b.value)
+
+
+def rmsmp_debug_measure_mfma6():
+    """MFMA-only 6-bit TOP/s of the current device."""
+    a = ctypes.c_double()
+    _check(_lib.rmsmp_debug_measure_mfma6(ctypes.byref(a)))
+    return float(a.value)
 
 
 # ---- storage helpers for callers (nibble packing of activation codes; no arithmetic of the method)

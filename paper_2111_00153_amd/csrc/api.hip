@@ -380,6 +380,13 @@ rmsmp_status rmsmp_debug_measure_peaks(double* mfma_int8_tops, double* copy_gbs)
   return RMSMP_OK;
 }
 
+rmsmp_status rmsmp_debug_measure_mfma6(double* mfma6_tops) {
+  if (!mfma6_tops) return fail(RMSMP_EINVAL, "debug_measure_mfma6: NULL output");
+  hipError_t e = (hipError_t)rmsmp::measure_mfma6(mfma6_tops);
+  if (e != hipSuccess) return hip_fail(e, "debug_measure_mfma6");
+  return RMSMP_OK;
+}
+
 rmsmp_status rmsmp_conv2d_workspace_size(const rmsmp_packed* Wp, const rmsmp_conv_desc* d, int32_t act_bits,
                                          size_t* bytes) {
   if (!bytes) return fail(RMSMP_EINVAL, "conv2d_workspace_size: NULL bytes");

@@ -237,6 +237,7 @@ int try_launch_conv_first(const GemmArgs& a, void* stream, bool* applied);
 int launch_im2col(const Im2colArgs& a, void* stream);
 // Machine rates (peaks.hip): MFMA-only int8 TOP/s and copy GB/s (read + written) of the current device.
 int measure_peaks(double* mfma_tops, double* copy_gbs);
+int measure_mfma6(double* tops);  // MFMA-only 6-bit TOP/s
 
 // Dynamic LDS above 64 KiB must be allowed per kernel once on every device.  `done` is the
 // kernel's own bit mask of devices that have it (one per launcher, a function-local static):
