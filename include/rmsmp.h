@@ -206,7 +206,10 @@ typedef struct {
  *   workspace  DEVICE scratch of at least rmsmp_conv2d_workspace_size() bytes, or NULL when
  *       that size is 0.  Layers whose C is a multiple of 16, and 8-bit layers with at
  *       most 4 input channels (a network's first layer), run without workspace: the
- *       im2col matrix is never materialised.  Other layers materialise it there.
+ *       im2col matrix is never materialised.  The others materialise it there, except that a layer
+ *       with 4-bit activations whose weights are also held as 6-bit operands (see
+ *       RMSMP_PACK_NO_OPERAND_FORM) is read where it lies, whatever C is (images of at most 65535
+ *       pixels a side, under 2 GiB): the workspace is asked for all the same, and left as it was.
  * Errors: EINVAL, ESHAPE (K mismatch, empty output), EWORKSPACE, EUNSUPPORTED, EHIP.
  */
 rmsmp_status rmsmp_conv2d(const rmsmp_packed* Wp, const void* X, const rmsmp_conv_desc* d,
@@ -221,11 +224,13 @@ rmsmp_status rmsmp_conv2d_workspace_size(const rmsmp_packed* Wp, const rmsmp_con
  * each exactly as rmsmp_conv2d computes it (Alg. 1 forward line, once per layer).  Meant for
  * the head of a residual stage of the ResNet-18 workload (Section 4.2): the stride-2 3x3
  * convolution and the stride-2 1x1 projection of the shortcut both read the stage's input.
- * When A is a 3x3 layer and B a 1x1 layer with the same 64, 128 or 256 input channels, 4-bit
- * activations, output kinds 0..2 and shapes the LDS-resident kernel takes, the two run as ONE
- * launch whose work-groups share the compute units (the short 1x1 layer runs in the shadow of
- * the 3x3 layer instead of paying a launch of its own); otherwise the library launches A and
- * then B on the stream.  Results are identical either way.
+ * With 4-bit activations and output kinds 0..2 the two run as ONE launch whose work-groups share
+ * the compute units (the short 1x1 layer runs in the shadow of the 3x3 layer instead of paying a
+ * launch of its own) in two cases: a 3x3 layer A and a 1x1 layer B with the same 64, 128 or 256
+ * input channels and shapes the LDS-resident kernel takes; and two small layers (a few images)
+ * whose weights are also held as 6-bit operands, C a multiple of 32, neither of them a plain GEMM
+ * (1x1, stride 1, no padding).  Otherwise the library launches A and then B on the stream.
+ * Results are identical either way.
  *
  *   WpA, dA, epA, YA / WpB, dB, epB, YB   as for rmsmp_conv2d; dA and dB must agree in B, C, H, W,
  *        epA and epB in act_scale, act_zero_point and act_bits; YA != YB.

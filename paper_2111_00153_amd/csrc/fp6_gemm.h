@@ -8,8 +8,10 @@
 // two E3M2 numbers whose factor 16 is the block scale of the instruction.  The block scales 4 and 8
 // undo the quarters and eighths, so the fp32 accumulators hold integers.  Layers are packed for this
 // kernel only if 15 * sum_k (|16 h| + |l|) of every row stays below 2^24: then every partial sum, in
-// whatever order the hardware adds, is an integer that fp32 holds.  (The instruction keeps such sums
-// exact: checked against integer arithmetic with accumulators up to 2^24.)
+// whatever order the hardware adds, is an integer that fp32 holds.  (That the instruction
+// keeps such sums exact whatever the mix of products is measured, not promised: the tests hold it
+// against integers with the largest and the smallest levels in one instruction, odd sums and both
+// signs, just below 2^24.)
 //
 // Weights are stored a second time in operand form when a layer is packed (0.75 bytes a weight, 1.5 in
 // tiles with Fixed-8 rows): the K loop has no weight decode at all, where the int8 kernels spend up to

@@ -134,8 +134,8 @@ def test_pair_of_resnet_stage_head_shapes(rm, oracle):
 
 
 def test_pair_falls_back_to_two_launches(rm, oracle):
-    """Shapes the two-layer launch does not exist for are launched one after the other, with the
-    same results: 96 channels (general kernel), and two 3x3 layers."""
+    """Shapes the int8 two-layer launch does not exist for are launched one after the other, with the
+    same results: 96 channels (general kernel, and the 6-bit kernels), and two 3x3 layers."""
     X, A, Bl = _pair(rm, oracle, 5, 2, 96, 12, 12, 64, 64, 2, 1)
     _run_all_kinds(rm, X, A, Bl, 1, "general")
     _run_all_kinds(rm, X, A, Bl, 1, "fp6_split", (0, 0, 0, 0))
