@@ -213,24 +213,30 @@ static float wide_us(const WidePlan& p) {
   const int taps = a.d.KH * a.d.KW;
   const bool x4 = p.xb == 4, nine = taps == 9;
   const float mfmas = (float)taps * p.cpt * p.g.nchunk / p.ks * 2 * p.xb;
-  const float lut = std::min(1.0f, 2.0f * a.w.class_tiles[TILE_NIB_LUT] / a.w.n_tiles);  // tile pairs with a table decode
-  const float kloop = mfmas * (x4 ? (nine ? 0.0167f : 0.02f) : (nine ? 0.0166f : 0.0173f) * (1.0f + 0.79f * lut));
-  const float stage = 1.2e-5f * p.g.patch_rows * p.g.row_stride;
+  // table-decoded tiles in the heaviest pair: tiles are sorted by class, pair y is tile y and tile n - 1 - y, so two of
+  // them meet only in the innermost pair.  (As a share of all tiles the 512-channel 3x3 layers at 7x7 with 35 to 40 % PoT
+  // rows came out 6 % too slow, and went to the 6-bit kernels: 8.2 us here, 8.6 there.)
+  const int n_tiles = a.w.n_tiles, lut0 = a.w.class_tiles[TILE_NIB_SHIFT], lut_tiles = a.w.class_tiles[TILE_NIB_LUT], inner = (n_tiles - 2) / 2;
+  const bool both = n_tiles >= 2 && lut0 <= inner && n_tiles - 1 - inner < lut0 + lut_tiles;
+  const float decode = both ? 0.928f : lut_tiles > 0 ? 0.47f : 0.0f;
+  const float kloop = mfmas * (x4 ? (nine ? 0.0179f : 0.021f) : 0.018f * (1.0f + decode));
+  const float stage = 1.34e-5f * p.g.patch_rows * p.g.row_stride;
   const bool out32 = a.ep.out_kind <= 1, unaligned = !out32 && a.M % 16 != 0, bias = a.ep.out_kind == 2 && a.ep.bias;
-  const float block = 0.556f + (out32 ? 1.03f : 0.0f) + (a.ep.out_kind == 3 ? 1.32f : 0.0f) + (unaligned ? 0.56f : 0.0f) + (bias ? 0.216f : 0.0f);
-  const float group = stage + kloop + (p.g.nchunk - 1) * (0.46f + stage) + 3.3e-5f * pw_xch_bytes(p.xb, p.ks, p.ks * p.nwt * p.ms) + 2.0f * p.xb / p.ks * block + (bias ? 0.504f : 0.0f);
-  const float extra = x4 ? mfmas * 0.0227f : mfmas * 0.021f + 0.234f * (group - kloop);  // one more on the same unit
+  const float block = 0.513f + (out32 ? 1.2f : 0.0f) + (a.ep.out_kind == 3 ? 1.29f : 0.0f) + (unaligned ? 0.685f : 0.0f) + (bias ? 0.189f : 0.0f);
+  const float group = stage + kloop + (p.g.nchunk - 1) * (0.459f + stage) + 2.98e-5f * pw_xch_bytes(p.xb, p.ks, p.ks * p.nwt * p.ms) + 2.0f * p.xb / p.ks * block + (bias ? 0.611f : 0.0f);
+  const float extra = x4 ? mfmas * 0.0218f : mfmas * 0.0195f + 0.216f * (group - kloop);  // one more on the same unit
   const int by_lds = (int)((160 * 1024) / p.lds), by_regs = x4 || p.g.nchunk > 1 ? 2 : 3;
   const int share = by_lds < by_regs ? by_lds : by_regs;
   // work-groups per compute unit: the column blocks are dealt out to the eight XCDs; tile pairs that a work-group
   // has no work for cost nothing
   const float per_unit = (float)((p.g.gx + 7) / 8) * ((a.w.n_tiles + 1) / 2) / p.ms / 32.0f;
-  const float n = per_unit < 1.0f ? 1.0f : std::ceil(per_unit - (share > 1 ? 0.15f : 0.0f));
-  const float full = std::floor(n / share), rest = n - full * share, round = group + (share - 1) * extra;
+  const float n = per_unit < 1.0f ? 1.0f : whole_up(per_unit - (share > 1 ? 0.15f : 0.0f));
+  const float full = whole_down(n / share), rest = n - full * share, round = group + (share - 1) * extra;
   float time = full * round + (rest > 0.0f ? group + (rest - 1.0f) * extra : 0.0f);
-  if (per_unit > share) time = 0.806f * time + 0.194f * per_unit / share * round;
+  if (per_unit < 1.0f) time *= 1.0f - 0.144f * (1.0f - per_unit);  // (fewer at the L2 and the memory)
+  if (per_unit > share) time = 0.821f * time + 0.179f * per_unit / share * round;
   const float megabytes = (float)((double)a.M * a.N * 4e-6);
-  return 2.23f + time + (out32 ? (a.N % 32 == 0 ? 0.135f : 0.153f) * megabytes : 0.0f) + (unaligned ? 0.17f * megabytes : 0.0f);
+  return 2.63f + time + (out32 ? (a.N % 32 == 0 ? 0.069f : 0.083f) * megabytes : 0.0f) + (unaligned ? 0.124f * megabytes : 0.0f);
 }
 
 static int launch_wide(const WidePlan& p, hipStream_t s) {

@@ -235,6 +235,13 @@ int fp6_pack(const HostPacked& h, const DevicePacked& dev, uint8_t* w, uint32_t*
 // First-layer kernel (conv_first.hip): 3 input channels, 8-bit activations, stride 2; same convention.
 int try_launch_conv_first(const GemmArgs& a, void* stream, bool* applied);
 int launch_im2col(const Im2colArgs& a, void* stream);
+// Up and down to whole numbers, of 0 to 2^31 (the estimates of every launch; ceilf and floorf are calls).
+inline float whole_down(float x) { return (float)(int)x; }
+inline float whole_up(float x) {
+  const float f = whole_down(x);
+  return f < x ? f + 1.0f : f;
+}
+
 // Machine rates (peaks.hip): MFMA-only int8 TOP/s and copy GB/s (read + written) of the current device.
 int measure_peaks(double* mfma_tops, double* copy_gbs);
 int measure_mfma6(double* tops);  // MFMA-only 6-bit TOP/s
