@@ -215,7 +215,7 @@ static float wide_us(const WidePlan& p) {
   const float mfmas = (float)taps * p.cpt * p.g.nchunk / p.ks * 2 * p.xb;
   // table-decoded tiles in the heaviest pair: tiles are sorted by class, pair y is tile y and tile n - 1 - y, so two of
   // them meet only in the innermost pair.  (As a share of all tiles the 512-channel 3x3 layers at 7x7 with 35 to 40 % PoT
-  // rows came out 6 % too slow, and went to the 6-bit kernels: 8.2 us here, 8.6 there.)
+  // rows came out 6 % too slow, and went to the 6-bit kernels: 8.2 us here, 8.9 there.)
   const int n_tiles = a.w.n_tiles, lut0 = a.w.class_tiles[TILE_NIB_SHIFT], lut_tiles = a.w.class_tiles[TILE_NIB_LUT], inner = (n_tiles - 2) / 2;
   const bool both = n_tiles >= 2 && lut0 <= inner && n_tiles - 1 - inner < lut0 + lut_tiles;
   const float decode = both ? 0.928f : lut_tiles > 0 ? 0.47f : 0.0f;
