@@ -127,7 +127,8 @@ void matrix_sizes(PyObject* o, int64_t* rows, int64_t* columns) {
   *columns = integer(PySequence_Fast_GET_ITEM(fast.o, 1));
 }
 
-// Runs f with the number of arguments checked and every C++ exception turned into a Python one; f returns the status.
+// Runs f with the number of arguments checked and every C++ exception turned into a Python one (which takes the
+// interpreter's lock: see Unlocked); f returns the status.
 template <class F>
 PyObject* guarded(Py_ssize_t n, Py_ssize_t want, F&& f) {
   if (n != want) {
@@ -140,18 +141,25 @@ PyObject* guarded(Py_ssize_t n, Py_ssize_t want, F&& f) {
   } catch (const python_error&) {  // (torch's, with the Python exception set)
   } catch (const std::exception& e) {
     PyErr_SetString(PyExc_RuntimeError, e.what());
+  } catch (...) {
+    PyErr_SetString(PyExc_RuntimeError, "unknown C++ exception");
   }
   return nullptr;
 }
 
+// While one lives, the thread runs without the interpreter's lock; it is taken back however the scope is left.
+struct Unlocked {
+  PyThreadState* const state = PyEval_SaveThread();
+  Unlocked() = default;
+  Unlocked(const Unlocked&) = delete;
+  ~Unlocked() { PyEval_RestoreThread(state); }
+};
+
 // The library's call itself, without the interpreter's lock.
 template <class F>
 rmsmp_status unlocked(F&& f) {
-  rmsmp_status st;
-  Py_BEGIN_ALLOW_THREADS
-  st = f();
-  Py_END_ALLOW_THREADS
-  return st;
+  const Unlocked scope;
+  return f();
 }
 
 // gemm(handle, X, N, ep, Y, stream)
