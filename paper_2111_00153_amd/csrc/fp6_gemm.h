@@ -70,8 +70,8 @@ struct Fp6Args {
     int32_t shift;
   } by_cb, by_kw, by_hw, by_ow;
   int32_t KW, H, W, OHW, OW, stride, pad;
-  GeluTable gelu;         // out_kind 3 only, as is
-  GeluBins bins;          // this (the tile kernel)
+  GeluTable gelu;         // break points of GELU output (out_kind 3)
+  GeluBins bins;          // the same cut into bins, for the tile kernel
 };
 
 // n / d for 0 <= n < 2^31
@@ -271,7 +271,7 @@ __device__ __forceinline__ void fp6_gelu(const v16f& v, const float (&m)[16], co
 
 // Finish NB 32x32 blocks of one weight tile.  meta: field 0 of the lane's first row; n: the lane's column of
 // block 0 (block j: + 32 j); n_rows: live rows of the lane's 16; gpos: its first grouped row.
-template <int NB>
+template <int NB, bool GELU>
 __device__ __forceinline__ void fp6_finish(const Fp6Args& a, v16f (&acc)[NB], const float* meta, const v2u* bins, int n_rows, int gpos, int n) {
   if (n_rows <= 0) return;
   float m[16];
@@ -282,7 +282,7 @@ __device__ __forceinline__ void fp6_finish(const Fp6Args& a, v16f (&acc)[NB], co
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[j][r] -= m[r];
   }
-  if (a.out_kind <= 1) {
+  if (!GELU && a.out_kind <= 1) {
     const __amdgpu_buffer_rsrc_t yr = fp6_rsrc(a.Y, a.y_bytes);
     uint32_t row[16];
     {
@@ -323,16 +323,18 @@ __device__ __forceinline__ void fp6_finish(const Fp6Args& a, v16f (&acc)[NB], co
   float bias[16];
   const bool has_bias = a.bias != nullptr;
   const bool relu_q = a.relu != 0 && !(a.out_inv_scale > 0.0f);
-  if (has_bias || relu_q || a.out_kind == 3) fp6_read16(meta + FM_BIAS * 64, bias);
+  if (GELU || has_bias || relu_q) fp6_read16(meta + FM_BIAS * 64, bias);
   const int half_m = a.M >> 1;
 #pragma unroll
   for (int j = 0; j < NB; ++j) {
     uint32_t packed[2];
-    if (a.out_kind == 3 && a.bins.n > 0) {
-      fp6_gelu(acc[j], m, bias, bins, a.bins.scale, a.bins.offset, packed);
-    } else if (a.out_kind == 3) {
-      constexpr int KOFF = (int)__builtin_offsetof(Fp6Args, gelu) - (int)__builtin_offsetof(GemmArgs, gelu);
-      gelu_requant_block<KOFF>(acc[j], m, bias, a.out_inv_scale, a.out_zero_point, packed);
+    if constexpr (GELU) {
+      if (a.bins.n > 0) {
+        fp6_gelu(acc[j], m, bias, bins, a.bins.scale, a.bins.offset, packed);
+      } else {
+        constexpr int KOFF = (int)__builtin_offsetof(Fp6Args, gelu) - (int)__builtin_offsetof(GemmArgs, gelu);
+        gelu_requant_block<KOFF>(acc[j], m, bias, a.out_inv_scale, a.out_zero_point, packed);
+      }
     } else if (relu_q) {  // (a bias of 0 where there is none)
       fp6_requant<true, true>(acc[j], m, bias, a.out_inv_scale, packed);
     } else if (has_bias) {
@@ -420,7 +422,7 @@ __device__ __forceinline__ uint4 fp6_fetch(const Fp6Args& a, __amdgpu_buffer_rsr
 // from LDS to each of them 4.8.  So what a product moves and widens counts as much as what it waits for: work-groups of eight waves
 // widen a column once per 512 rows.  (512 x 128 / 256 x 128 / 256 x 64 outputs: 8192 x 4096 x 8192 167 / 171 / 217 us; two
 // columns of waves with the weights through LDS, 256 x 256: 186.)  On short K the first reads and the epilogue: 6 us.
-template <int TN, int WM, int WN, bool CONV, bool RAGGED>
+template <int TN, int WM, int WN, bool CONV, bool RAGGED, bool GELU>
 __device__ __forceinline__ void fp6_k_loop(const Fp6Args& a, uint8_t* smem, v16f (&acc)[2][TN], const Fp6Pair& pair, int n0) {
   constexpr int NW = WM * WN, NT = LANES * NW, BN = 32 * TN * WN;
   constexpr int PP = BN * 4 / NT;  // 16-byte pieces a thread stages per 128 k
@@ -478,7 +480,7 @@ __device__ __forceinline__ void fp6_k_loop(const Fp6Args& a, uint8_t* smem, v16f
   load_w(2, ring[2]), load_w(3, ring[3]);
   __builtin_amdgcn_sched_barrier(0);
   const float bias = fp6_stage_meta(a, pair, row, meta, lane);
-  if (a.out_kind == 3 && wave == 0) fp6_stage_bins(a.bins, (v2u*)(stage + 2 * BUF), lane);
+  if (GELU && wave == 0) fp6_stage_bins(a.bins, (v2u*)(stage + 2 * BUF), lane);
   __builtin_amdgcn_sched_barrier(0);
 
 #pragma unroll
@@ -607,7 +609,9 @@ constexpr size_t fp6_lds() {
   return (size_t)WM * WN * FP6_META_BYTES + 2 * (size_t)(TN * WN) * 2 * FP6_LDS_FRAG;
 }
 
-template <int TN, int WM, int WN, bool CONV, bool RAGGED>
+// GELU: out_kind 3, chosen by the host.  An instantiation of its own: beside the other outputs the GELU code cost all of
+// them registers (PLACEHOLDER).
+template <int TN, int WM, int WN, bool CONV, bool RAGGED, bool GELU>
 // (waves per SIMD: what the registers of the K loop leave room for)
 __global__ __launch_bounds__(LANES * WM * WN, TN == 4 || (TN == 2 && WN == 4) ? 2 : TN == 2 || WN > 1 ? 3 : 4) void fp6_tile_kernel(Fp6Args a) {
   extern __shared__ __attribute__((aligned(16))) uint8_t smem_raw[];
@@ -620,7 +624,7 @@ __global__ __launch_bounds__(LANES * WM * WN, TN == 4 || (TN == 2 && WN == 4) ? 
   const Fp6Pair pair = fp6_pair(a, q < a.pairs ? q : a.pairs - 1);
   const int n0 = bx * (32 * TN * WN);
   v16f acc[2][TN];
-  fp6_k_loop<TN, WM, WN, CONV, RAGGED>(a, smem_raw, acc, pair, n0);
+  fp6_k_loop<TN, WM, WN, CONV, RAGGED, GELU>(a, smem_raw, acc, pair, n0);
   if (q >= a.pairs) return;
   if (pair.two) {
 #pragma unroll
@@ -635,7 +639,7 @@ __global__ __launch_bounds__(LANES * WM * WN, TN == 4 || (TN == 2 && WN == 4) ? 
     const int t = i ? pair.t1 : pair.t0;
     if (t < 0) break;
     const int rows = lane_rows(t == a.n_tiles - 1 ? a.last_rows : TILE_M, lane);
-    fp6_finish<TN>(a, acc[i], mp + i * TILE_M, (const v2u*)(smem_raw + fp6_lds<TN, WM, WN>()), rows, t * TILE_M + 16 * (lane >> 5), n);
+    fp6_finish<TN, GELU>(a, acc[i], mp + i * TILE_M, (const v2u*)(smem_raw + fp6_lds<TN, WM, WN>()), rows, t * TILE_M + 16 * (lane >> 5), n);
   }
 }
 

@@ -1,0 +1,59 @@
+"""Registers and scratch memory of the built kernels, read from the library's own code objects: what the launch bounds and
+the estimates of a launch's time assume of them.  CPU only."""
+import os
+import re
+import struct
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+LIB = os.path.join(ROOT, "paper_2111_00153_amd", "librmsmp.so")
+READELF = os.path.join(os.environ.get("ROCM_PATH", "/opt/rocm"), "llvm", "bin", "llvm-readelf")
+MAGIC = b"__CLANG_OFFLOAD_BUNDLE__"
+
+
+def _code_objects(data):
+    """The gfx950 objects of the bundles in a library: header, then (offset, size, name) of each entry."""
+    at = data.find(MAGIC)
+    while at >= 0:
+        count, = struct.unpack_from("<Q", data, at + len(MAGIC))
+        entry = at + len(MAGIC) + 8
+        for _ in range(count):
+            offset, size, length = struct.unpack_from("<QQQ", data, entry)
+            name = data[entry + 24:entry + 24 + length]
+            entry += 24 + length
+            if b"gfx950" in name and size:
+                yield data[at + offset:at + offset + size]
+        at = data.find(MAGIC, at + len(MAGIC))
+
+
+@pytest.fixture(scope="module")
+def kernels(tmp_path_factory):
+    """{(name, template arguments): (registers, bytes of scratch)}"""
+    found = {}
+    path = tmp_path_factory.mktemp("code") / "object"
+    with open(LIB, "rb") as f:
+        data = f.read()
+    for obj in _code_objects(data):
+        path.write_bytes(obj)
+        notes = subprocess.run([READELF, "--notes", str(path)], capture_output=True, text=True, check=True).stdout
+        for block in re.split(r"\n  - \.agpr_count:", notes)[1:]:
+            def value(key):
+                return re.search(r"\." + key + r":\s+(\S+)", block).group(1)
+            m = re.match(r"_ZN5rmsmp\d+([a-z0-9_]+_kernel)I((?:L[ib]\d+E)+)E", value("name"))
+            if m:
+                arguments = tuple(int(v) for v in re.findall(r"L[ib](\d+)E", m.group(2)))
+                found[m.group(1), arguments] = (int(value("vgpr_count")), int(value("private_segment_fixed_size")))
+    return found
+
+
+def _named(kernels, name):
+    return {arguments: use for (n, arguments), use in kernels.items() if n == name}
+
+
+def test_fp6_tile_kernels_keep_their_sums_in_registers(kernels):
+    """No instantiation (blocks per wave, waves along rows, along columns, convolution, ragged, GELU) spills."""
+    tile = _named(kernels, "fp6_tile_kernel")
+    assert {a: use for a, use in tile.items() if use[1] != 0} == {}
+    assert len(tile) == 8 * 2 * 2 * 2
