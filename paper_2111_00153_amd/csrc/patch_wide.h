@@ -51,13 +51,12 @@ constexpr int PW_PATCH_UNROLL = 6;  // 16-byte patch pieces in flight per thread
 // of five is one read, one decode and four registers less for the former.
 constexpr int pw_batch(int taps) { return taps == 9 ? 5 : PW_PATCH_UNROLL; }
 constexpr bool wide_has_gelu(int taps, int xb) { return taps == 1 && xb == 2; }
-// Whether the lean epilogue takes biases: not where two layers share a launch (the heads of 64 channels without a bias took
-// 12.6 instead of 12.1 us with that code beside theirs).
-#ifdef RMSMP_WIDE_PAIR
-constexpr bool WIDE_LEAN_BIAS = false;
-#else
-constexpr bool WIDE_LEAN_BIAS = true;
-#endif
+// Whether a launch's 4-bit output goes through the lean epilogue (wide_wave, 5): no ReLU beyond the clamp at code 0 (a positive
+// output scale makes the two the same), the whole layer a multiple of 16 rows and the output 8-byte aligned.
+template <class Ep>
+__host__ __device__ __forceinline__ bool wide_lean(const Ep& ep, int64_t M, const void* Y) {
+  return ep.out_kind == 2 && !(ep.relu != 0 && !(ep.out_inv_scale > 0.0f)) && (M & 15) == 0 && (((uintptr_t)Y) & 7) == 0;
+}
 // Row metadata of a tile pair in LDS, field by field [field][64 rows]: rowscale bits, rowsum, original
 // row, grouped position, and two values formed once per work-group for the lean 4-bit epilogue: the
 // row's multiplier rowscale * activation scale (* 1/16 for shift-decoded tiles) and zero point * rowsum
@@ -163,7 +162,7 @@ __device__ __forceinline__ uint4 wide_load_piece(const WidePatchLoads& pl, int i
 }
 
 // Everything one wave does.  KIND0 / KIND1: storage classes of its two weight tiles.
-template <int TAPS, int CPT, int XB, int KS, int NWT, int MS, bool DEEP, int KIND0, int KIND1>
+template <int TAPS, int CPT, int XB, int KS, int NWT, int MS, bool DEEP, bool BIAS, int KIND0, int KIND1>
 __device__ __forceinline__ void wide_wave(const GemmArgs& a, const EpArgs& ea, const WideGeom& g, int bx, int pair,
                                           bool pair_live, WidePatchLoads& pl) {
   extern __shared__ __attribute__((aligned(16))) uint8_t smem_raw[];
@@ -540,12 +539,9 @@ __device__ __forceinline__ void wide_wave(const GemmArgs& a, const EpArgs& ea, c
   constexpr int TPW = OWN >= PW_XB ? OWN / PW_XB : 1;  // weight tiles this wave finishes
   constexpr int BPT = OWN / TPW;                        // blocks per such tile
   constexpr int CH = BPT < 2 ? BPT : 2;                 // finished two at a time (register pressure)
-  // The common case gets an epilogue of its own, chosen once per wave: 4-bit output, no
-  // ReLU beyond the clamp at code 0 (a positive output scale makes the two the same), the whole
-  // layer a multiple of 16 rows and the output 8-byte aligned.  Everything else goes through the
-  // general finish_tiles.
-  const bool lean = ea.out_kind == 2 && (WIDE_LEAN_BIAS || ea.bias == nullptr) && !(ea.relu != 0 && !(ea.out_inv_scale > 0.0f)) &&
-                    (ea.M & 15) == 0 && (((uintptr_t)ea.Y) & 7) == 0;
+  // The common case gets an epilogue of its own, chosen once per wave: wide_lean without a bias.  The same with a bias is an
+  // instantiation (BIAS) that has nothing else.  Everything else goes through the general finish_tiles.
+  const bool lean = BIAS || (ea.bias == nullptr && wide_lean(ea, ea.M, ea.Y));
 #pragma unroll
   for (int ti = 0; ti < TPW; ++ti) {
     const int q0 = kq * OWN + ti * BPT;  // first block
@@ -560,20 +556,17 @@ __device__ __forceinline__ void wide_wave(const GemmArgs& a, const EpArgs& ea, c
     if (lean) {
       // 4-bit codes, no separate ReLU, all 16 rows of the lane alive: multipliers and
       // zero-point terms come ready from LDS, a pixel's 16 codes leave as one 8-byte store
-      auto finish_lean = [&](auto bias_tag) {
-        constexpr bool BIAS = decltype(bias_tag)::value;
-        float brow[16];
-        if constexpr (BIAS) {
-          // One read a lane, row lane % 32 of the tile, and each lane takes its sixteen from the others (every lane takes part:
-          // rows alive come from lanes whose own rows may not be).  With sixteen reads a lane, as in finish_tiles, 64 to 64 channels,
-          // 64 x 56 x 56, took 15.9 us, so 13.7 (12.3 without a bias).  Asked for in front of the K loop or of the exchange the
-          // read is hidden, but launches without a bias took 1.5 % longer.
-          const int orig = (meta_pair + my_tile * TILE_M)[2 * (2 * TILE_M) + (lane & 31)];
-          const int own = __float_as_int(as_global(ea.bias)[orig < 0 ? 0 : orig]);
+      float brow[16];
+      if constexpr (BIAS) {
+        // One read a lane, row lane % 32 of the tile, and each lane takes its sixteen from the others (every lane takes part:
+        // rows alive come from lanes whose own rows may not be).  With sixteen reads a lane, as in finish_tiles, 64 to 64 channels,
+        // 64 x 56 x 56, took 15.9 us, so 13.0 (12.1 without a bias).
+        const int orig = (meta_pair + my_tile * TILE_M)[2 * (2 * TILE_M) + (lane & 31)];
+        const int own = __float_as_int(as_global(ea.bias)[orig < 0 ? 0 : orig]);
 #pragma unroll
-          for (int r = 0; r < 16; ++r) brow[r] = __int_as_float(__builtin_amdgcn_ds_bpermute(4 * (16 * (lane >> 5) + r), own));
-        }
-        if (n_rows != 16) return;
+        for (int r = 0; r < 16; ++r) brow[r] = __int_as_float(__builtin_amdgcn_ds_bpermute(4 * (16 * (lane >> 5) + r), own));
+      }
+      if (n_rows == 16) {
         float mrow[16];
         int crow[16];
         const float4* mp = (const float4*)(rm.base + 4 * (2 * TILE_M));
@@ -603,11 +596,7 @@ __device__ __forceinline__ void wide_wave(const GemmArgs& a, const EpArgs& ea, c
           const int64_t n = col0 + 32 * o;
           if (n < ea.N) *(RMSMP_GLOBAL v2u*)(out0 + n * (ea.M / 2)) = (v2u){packed[0], packed[1]};
         }
-      };
-      if (!WIDE_LEAN_BIAS || __builtin_expect(ea.bias == nullptr, 1))
-        finish_lean(std::false_type{});
-      else if constexpr (WIDE_LEAN_BIAS)
-        finish_lean(std::true_type{});
+      }
       continue;
     }
     if constexpr (WIDE_GELU) {
@@ -664,7 +653,7 @@ __device__ __forceinline__ WideFirst wide_first_of(const GemmArgs& a, const Wide
   return WideFirst{a.X, g.gx, g.gy, g.magic_hw, g.magic_ow, a.d.H, a.d.W, a.OH, a.OW, a.d.stride, a.d.pad, g.gather, a.d.B, g.pix_bytes, a.N};
 }
 
-template <int TAPS, int CPT, int XB, int KS, int NWT, int MS, bool DEEP>
+template <int TAPS, int CPT, int XB, int KS, int NWT, int MS, bool DEEP, bool BIAS>
 __device__ __forceinline__ void wide_kernel_impl(const WideFirst& f, const GemmArgs& a, const WideGeom& g, const unsigned block_id) {
   RMSMP_PHASE(0);
   // Work-group id -> (pixel tile bx, row block by).  Consecutive ids go to different XCDs, each
@@ -710,7 +699,7 @@ __device__ __forceinline__ void wide_kernel_impl(const WideFirst& f, const GemmA
   auto kind_of = [&](int mt) { return mt < a.w.class_tiles[0] ? 0 : mt < a.w.class_tiles[0] + a.w.class_tiles[1] ? 1 : 2; };
   const int k0 = kind_of(pair), k1 = kind_of(a.w.n_tiles - 1 - pair);
 #define RMSMP_WIDE(K0, K1) \
-  if (k0 == K0 && k1 == K1) wide_wave<TAPS, CPT, XB, KS, NWT, MS, DEEP, K0, K1>(a, ea, g, bx, pair, pair_live, pl);
+  if (k0 == K0 && k1 == K1) wide_wave<TAPS, CPT, XB, KS, NWT, MS, DEEP, BIAS, K0, K1>(a, ea, g, bx, pair, pair_live, pl);
   RMSMP_WIDE(TILE_NIB_SHIFT, TILE_NIB_SHIFT)
   else RMSMP_WIDE(TILE_NIB_SHIFT, TILE_NIB_LUT)
   else RMSMP_WIDE(TILE_NIB_SHIFT, TILE_I8)
@@ -721,9 +710,12 @@ __device__ __forceinline__ void wide_kernel_impl(const WideFirst& f, const GemmA
   RMSMP_PHASE_FLUSH();
 }
 
-template <int TAPS, int CPT, int XB, int KS, int NWT, int MS, bool DEEP>
+// BIAS: the lean epilogue with a bias and nothing else, chosen by the host.  An instantiation of its own: beside the other
+// epilogues its code cost launches without a bias registers (64 pixels a wave, split in two: 169 for 167, two waves a SIMD
+// instead of three, 256 x 128 x 50176 13.3 us for 11.0) or spilled (up to 231 of them).
+template <int TAPS, int CPT, int XB, int KS, int NWT, int MS, bool DEEP, bool BIAS>
 __global__ __launch_bounds__(LANES * KS * NWT * MS, KS * NWT * MS == 8 ? 1 : 2) void conv_wide_kernel(WIDE_FIRST_PARAMS, GemmArgs a, WideGeom g) {
-  wide_kernel_impl<TAPS, CPT, XB, KS, NWT, MS, DEEP>(WIDE_FIRST_UNPACK(), a, g, blockIdx.x);
+  wide_kernel_impl<TAPS, CPT, XB, KS, NWT, MS, DEEP, BIAS>(WIDE_FIRST_UNPACK(), a, g, blockIdx.x);
 }
 
 // Two layers that read the same input tensor as one launch: a 3x3 layer and a 1x1 layer with the
@@ -732,7 +724,8 @@ __global__ __launch_bounds__(LANES * KS * NWT * MS, KS * NWT * MS == 8 ? 1 : 2) 
 // first blocks_a work-groups run the 3x3 layer's code, the others the 1x1 layer's; the two kinds
 // share compute units, so the short 1x1 work-groups run in the shadow of the long ones instead
 // of paying a launch of their own.  Neither layer may use the GELU epilogue (its table is read
-// from the start of the kernel arguments).
+// from the start of the kernel arguments).  Biases go through the general epilogue: with the lean one for them beside the
+// other epilogues the heads of 64 channels without a bias took 12.6 instead of 12.1 us.
 struct WidePairSplit {
   int xa, ka, na, ma;  // 3x3 layer: pixel blocks per wave, K split, side by side, tile pairs
   int xb, kb, nb, mb;  // 1x1 layer
@@ -748,9 +741,9 @@ __global__ __launch_bounds__(LANES * 4, 2) void conv_wide_pair_kernel(WIDE_FIRST
   // (the leading arguments are the 3x3 layer's; the 1x1 layer's work-groups read theirs from memory)
   constexpr WidePairSplit sp = wide_pair_split(CPT);
   if (blockIdx.x < blocks_a)
-    wide_kernel_impl<9, CPT, sp.xa, sp.ka, sp.na, sp.ma, false>(WIDE_FIRST_UNPACK(), a, ga, blockIdx.x);
+    wide_kernel_impl<9, CPT, sp.xa, sp.ka, sp.na, sp.ma, false, false>(WIDE_FIRST_UNPACK(), a, ga, blockIdx.x);
   else
-    wide_kernel_impl<1, CPT, sp.xb, sp.kb, sp.nb, sp.mb, false>(wide_first_of(b, gb), b, gb, blockIdx.x - blocks_a);
+    wide_kernel_impl<1, CPT, sp.xb, sp.kb, sp.nb, sp.mb, false, false>(wide_first_of(b, gb), b, gb, blockIdx.x - blocks_a);
 }
 
 struct WidePlan {
@@ -770,15 +763,21 @@ struct WidePlan {
       (uint32_t)(p).a.d.stride | ((uint32_t)(p).a.d.pad << 8) | ((uint32_t)(p).g.gather << 16), (int)(p).a.d.B,        \
       (p).g.pix_bytes, (int)(p).a.N
 
+template <int TAPS, int CPT, int XB, int KS, int NWT, int MS, bool DEEP, bool BIAS>
+inline int launch_wide_ep(const WidePlan& p, hipStream_t s) {
+  static std::atomic<uint64_t> allowed{0};
+  if (const int rc = allow_large_lds((const void*)conv_wide_kernel<TAPS, CPT, XB, KS, NWT, MS, DEEP, BIAS>, allowed)) return rc;
+  hipLaunchKernelGGL((conv_wide_kernel<TAPS, CPT, XB, KS, NWT, MS, DEEP, BIAS>), dim3(p.blocks), dim3(LANES * KS * NWT * MS), p.lds, s, WIDE_FIRST_ARGS(p), p.a, p.g);
+  return (int)hipGetLastError();
+}
+
 template <int TAPS, int CPT, int XB, int KS, int NWT, int MS, bool DEEP>
 inline int launch_wide_t(const WidePlan& p, hipStream_t s) {
   if constexpr (CPT % KS != 0 || TAPS * (CPT / KS) < 2) {
     return (int)hipErrorInvalidValue;
   } else {
-    static std::atomic<uint64_t> allowed{0};
-    if (const int rc = allow_large_lds((const void*)conv_wide_kernel<TAPS, CPT, XB, KS, NWT, MS, DEEP>, allowed)) return rc;
-    hipLaunchKernelGGL((conv_wide_kernel<TAPS, CPT, XB, KS, NWT, MS, DEEP>), dim3(p.blocks), dim3(LANES * KS * NWT * MS), p.lds, s, WIDE_FIRST_ARGS(p), p.a, p.g);
-    return (int)hipGetLastError();
+    if (p.a.ep.bias != nullptr && wide_lean(p.a.ep, p.a.M, p.a.Y)) return launch_wide_ep<TAPS, CPT, XB, KS, NWT, MS, DEEP, true>(p, s);
+    return launch_wide_ep<TAPS, CPT, XB, KS, NWT, MS, DEEP, false>(p, s);
   }
 }
 

@@ -1,7 +1,6 @@
 // The two-layer launch of the wide LDS-resident kernel (a 3x3 layer and a 1x1 layer on the same
 // input) for one channel count; compiled once per count with -DRMSMP_WIDE_CPT=.. so that the
 // counts build in parallel.
-#define RMSMP_WIDE_PAIR 1
 #include "patch_wide.h"
 
 #define RMSMP_PAIR_CAT2(a) launch_wide_pair_##a

@@ -57,3 +57,14 @@ def test_fp6_tile_kernels_keep_their_sums_in_registers(kernels):
     tile = _named(kernels, "fp6_tile_kernel")
     assert {a: use for a, use in tile.items() if use[1] != 0} == {}
     assert len(tile) == 8 * 2 * 2 * 2
+
+
+def test_lds_resident_kernels_without_a_bias_have_the_registers_their_estimates_assume(kernels):
+    """Template arguments: taps, K steps, pixel blocks, K split, side by side, tile pairs, in parts, bias.  With 64 pixels a wave,
+    K split and two tile pairs three work-groups share a compute unit (at most 168 registers; 768 channels have always taken
+    169); a wave with all of K spills nothing."""
+    wide = {a: use for a, use in _named(kernels, "conv_wide_kernel").items() if not a[-1]}
+    three = {a: use for a, use in wide.items() if a[2:6] == (2, 2, 1, 2) and not a[6] and a[1] != 24}
+    assert {a: use for a, use in three.items() if use[0] > 168} == {} and len(three) == 7
+    whole = {a: use for a, use in wide.items() if a[3] == 1}
+    assert {a: use for a, use in whole.items() if use[1] != 0} == {} and len(whole) > 20
