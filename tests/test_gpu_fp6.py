@@ -12,6 +12,10 @@ torch = pytest.importorskip("torch")
 
 DEV = "cuda:0"
 SHAPES = list(range(1, 10))
+# the dispatch record of each: the tile kernel's blocks per wave, waves along the rows, along the columns; the split kernels'
+# waves and, on half tiles, blocks of 16 columns
+TILES = {1: (4, 4, 1), 2: (2, 2, 2), 3: (2, 1, 4), 4: (2, 4, 1), 5: (1, 2, 1), 6: (1, 1, 4), 14: (4, 8, 1), 15: (2, 2, 1)}
+SPLITS = {7: (4, 0, 0), 8: (8, 0, 0), 9: (16, 0, 0), 16: (4, 1, 0), 17: (8, 1, 0), 18: (4, 2, 0), 19: (8, 2, 0)}
 
 
 @pytest.fixture(scope="module")
@@ -20,6 +24,12 @@ def rm():
     assert torch.cuda.is_available(), "these tests need the GPU"
     yield m
     m.rmsmp_debug_set_wave_split(0, 0, 0, 0)
+
+
+def _ran(rm, shape):
+    """The last launch was of the shape that was asked for."""
+    kernel, numbers = rm.rmsmp_debug_last_dispatch()
+    assert (kernel, numbers[:3]) == (("fp6_tile", TILES[shape]) if shape in TILES else ("fp6_split", SPLITS[shape]))
 
 
 def _to_dev(a):
@@ -75,9 +85,13 @@ def test_gemm_every_work_group_shape(rm, oracle, shape, M, K, N, ratio):
     acc = oracle.gemm_acc(ref["wint"], x.astype(np.int32))
     p = rm.rmsmp_pack_weights(W, scheme, flags=rm.PACK_POT_AS_INT8 if shape == 2 else 0)
     X = _to_dev(rm.pack_u4(x))
+
+    def call(Y, ep):
+        rm.rmsmp_gemm(p, X, N, ep, Y)
+        _ran(rm, shape)
     rm.rmsmp_debug_set_wave_split(0, shape, 0, 0)
     try:
-        _check_outputs(rm, oracle, lambda Y, ep: rm.rmsmp_gemm(p, X, N, ep, Y), p, M, N, ref, acc, (3 * shape) % 16, bias, shape % 3 == 0)
+        _check_outputs(rm, oracle, call, p, M, N, ref, acc, (3 * shape) % 16, bias, shape % 3 == 0)
     finally:
         rm.rmsmp_debug_set_wave_split(0, 0, 0, 0)
         p.free()
@@ -117,9 +131,13 @@ def test_conv_every_work_group_shape(rm, oracle, shape, geom, M):
     X = _to_dev(rm.pack_u4(x))
     need = rm.rmsmp_conv2d_workspace_size(p, d, 4)
     ws = torch.empty((need,), dtype=torch.uint8, device=DEV) if need else None
+
+    def call(Y, ep):
+        rm.rmsmp_conv2d(p, X, d, ep, Y, ws)
+        _ran(rm, shape)
     rm.rmsmp_debug_set_wave_split(0, shape, 0, 0)
     try:
-        _check_outputs(rm, oracle, lambda Y, ep: rm.rmsmp_conv2d(p, X, d, ep, Y, ws), p, M, N, ref, acc, z, bias, shape % 3 == 0)
+        _check_outputs(rm, oracle, call, p, M, N, ref, acc, z, bias, shape % 3 == 0)
     finally:
         rm.rmsmp_debug_set_wave_split(0, 0, 0, 0)
         p.free()
@@ -209,7 +227,7 @@ def test_gelu_codes_around_every_break_point(rm, oracle, shape, s_out, z_out):
     rm.rmsmp_debug_set_wave_split(0, shape, 0, 0)
     try:
         rm.rmsmp_gemm(p, _to_dev(rm.pack_u4(x)), N, rm.make_epilogue(0.05, 0, 4, bias_d, False, rm.OUT_GELU_U4, inv, z_out), Y)
-        assert rm.rmsmp_debug_last_dispatch()[0] == "fp6_tile"
+        _ran(rm, shape)
     finally:
         rm.rmsmp_debug_set_wave_split(0, 0, 0, 0)
     torch.cuda.synchronize()
@@ -353,7 +371,7 @@ def test_mixed_sums_just_below_what_fp32_holds(rm, oracle, scheme_code, shape):
     try:
         Y = torch.full((M, N), -777, dtype=torch.int32, device=DEV)
         rm.rmsmp_gemm(p, _to_dev(rm.pack_u4(x)), N, rm.make_epilogue(0.05, 0, 4, None, False, rm.OUT_INT32), Y)
-        assert rm.rmsmp_debug_last_dispatch()[0] == ("fp6_tile" if shape <= 6 else "fp6_split")
+        _ran(rm, shape)
     finally:
         rm.rmsmp_debug_set_wave_split(0, 0, 0, 0)
     torch.cuda.synchronize()

@@ -128,6 +128,7 @@ def test_pair_runs_as_one_launch_and_matches_oracle(rm, oracle, C, MA, MB, H, W,
 def test_pair_on_half_tiles(rm, oracle, C, MA, MB, H, W, shape):
     X, A, Bl = _pair(rm, oracle, 1100 + C, 3, C, H, W, MA, MB, 2, 3)
     _run_all_kinds(rm, X, A, Bl, 3, "fp6_split_pair", (0, shape, 0, 0))
+    assert rm.rmsmp_debug_last_dispatch()[1][:2] == {16: (4, 1), 17: (8, 1), 18: (4, 2), 19: (8, 2)}[shape]  # waves, blocks of 16 columns
     A.p.free()
     Bl.p.free()
 
