@@ -56,9 +56,10 @@ def _compile(unit, extra=()):
 def _build_pycall():
     torch_dir = os.path.dirname(importlib.util.find_spec("torch").origin)
     inc, lib = os.path.join(torch_dir, "include"), os.path.join(torch_dir, "lib")
-    subprocess.check_call(["hipcc", "-x", "c++", "-O2", "-std=c++17", "-fPIC", "-shared", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM", "-Wno-everything",
-                           "-I" + inc, "-I" + os.path.join(inc, "torch", "csrc", "api", "include"), "-I" + sysconfig.get_paths()["include"],
-                           "-I" + os.path.join(os.environ.get("ROCM_PATH", "/opt/rocm"), "include"), "-I" + os.path.join(ROOT, "include"), os.path.join(HERE, PYCALL_SOURCE), "-o", PYCALL,
+    subprocess.check_call(["hipcc", "-x", "c++", "-O2", "-std=c++17", "-fPIC", "-shared", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM", "-Wall", "-Wextra",
+                           # (warnings for the module, not for the headers of torch, the interpreter and ROCm)
+                           "-isystem", inc, "-isystem", os.path.join(inc, "torch", "csrc", "api", "include"), "-isystem", sysconfig.get_paths()["include"],
+                           "-isystem", os.path.join(os.environ.get("ROCM_PATH", "/opt/rocm"), "include"), "-I" + os.path.join(ROOT, "include"), os.path.join(HERE, PYCALL_SOURCE), "-o", PYCALL,
                            "-L" + lib, "-ltorch_python", "-ltorch_cpu", "-lc10", "-lc10_hip"], cwd=HERE)
 
 
