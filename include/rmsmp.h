@@ -306,7 +306,9 @@ rmsmp_status rmsmp_ste_backward(const float* W, const float* alpha, const float*
  *   With pixel_blocks = 0 the request is for the FP6 kernels: k_split = 1..6 a work-group shape of the
  *   tile kernel, 7, 8, 9 the split kernel with 4, 8, 16 waves (8 and 9 also for the two layers of a pair),
  *   10..13 a work-group shape of the skinny kernel, 14 and 15 two more of the tile kernel, 16..19 the split kernel
- *   on half weight tiles with 4 or 8 waves and 16 (16, 17) or 32 columns (18, 19; also for a pair); side_by_side = 1 instead: the int8 kernels only
+ *   on half weight tiles with 4 or 8 waves and 16 (16, 17) or 32 columns (18, 19; also for a pair), 20..24 a shape of the tile
+ *   kernel with neighbouring tiles joined in a wave (even numbers of tiles with Fixed-8 rows, no GELU; 1 elsewhere);
+ *   side_by_side = 1 instead: the int8 kernels only
  *   (a convolution that needs a workspace is then lowered into it), 2: the general kernel only.
  * rmsmp_debug_last_dispatch -- what the calling thread's last rmsmp_gemm / rmsmp_conv2d /
  *   rmsmp_conv2d_pair ran (a pair that went out as two launches: the second one):
@@ -318,7 +320,7 @@ rmsmp_status rmsmp_ste_backward(const float* W, const float* alpha, const float*
  *   8 FP6 split: waves, blocks of 16 columns of a half tile's work-group (0: whole tiles, 32 columns), 0, variant,
  *   9 FP6 split with two layers in one launch: as 8,
  *   10 split on int8 instructions (8-bit activations): as 8;
- *   variant: 1 for a convolution, plus 2 where a column (pixel) is no multiple of 16 bytes.  What
+ *   variant: 1 for a convolution, plus 2 where a column (pixel) is no multiple of 16 bytes, plus 4 where tiles are joined.  What
  *   is not named is 0.
  * Errors: EINVAL (negative value, NULL).
  */

@@ -6,7 +6,7 @@
 // the E2M3 bit pattern of the same number (value code / 8); Fixed-4 levels (|q| <= 7) and PoT-4 levels
 // (0, +-1, .., +-64) are E3M2 numbers (value q / 4); a Fixed-8 level is 16 h + l with |h|, |l| <= 8,
 // two E3M2 numbers.  The accumulators of the tile kernel hold 1/32 of integers (4 and 8 are made up for in the row's
-// multiplier, 16 when the two sums of a Fixed-8 tile are added), those of the split kernel, which gives the instruction these
+// multiplier, 16 when the two sums of a Fixed-8 tile are added, or as a block scale where they share an accumulator), those of the split kernel, which gives the instruction these
 // factors as block scales, integers.  Layers are packed for this
 // kernel only if 15 * sum_k (|16 h| + |l|) of every row stays below 2^24: then every partial sum, in
 // whatever order the hardware adds, is an integer that fp32 holds.  (That the instruction
@@ -92,6 +92,11 @@ __device__ __forceinline__ v8i fp6_operand(const Fp6Frag& f) {
 // channels, 16 images of 57 x 57: 24.2 -> 18.5 us).
 __device__ __forceinline__ v16f fp6_mfma(const Fp6Frag& w, const Fp6Frag& x, v16f acc) {
   return __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(fp6_operand(w), fp6_operand(x), acc, 3, 2, 0, 0, 0, 0);
+}
+
+// acc += 16 x weights x activations: hi parts, in the accumulators of the lo parts
+__device__ __forceinline__ v16f fp6_mfma_hi(const Fp6Frag& w, const Fp6Frag& x, v16f acc) {
+  return __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(fp6_operand(w), fp6_operand(x), acc, 3, 2, 0, 0x83838383, 0, 0x7f7f7f7f);
 }
 
 // Sixteen 4-bit codes (two words, eight nibbles each) to sixteen 6-bit fields (three words).  Field order
@@ -180,6 +185,14 @@ __device__ __forceinline__ Fp6Pair fp6_pair(const Fp6Args& a, int q) {
     p.stride = FP6_FRAG;
   }
   return p;
+}
+
+// The other way to give tiles to waves (fp6_joined_kernel; an even number of tiles): two neighbouring ones to each, whatever they
+// hold.  A tile with Fixed-8 rows is then two operands a K step for one accumulator.
+__device__ __forceinline__ Fp6Pair fp6_pair_joined(const Fp6Args& a, int q) {
+  const int64_t one = (int64_t)a.nsteps * FP6_FRAG;
+  auto off = [&](int t) { return (t <= a.n_single ? t : 2 * t - a.n_single) * one; };
+  return Fp6Pair{2 * q, 2 * q + 1, false, off(2 * q), off(2 * q + 1), FP6_FRAG};
 }
 
 // Row data of a pair, a row a lane: multiplier rowscale * act_scale * 32, zero point * row sum / 32 (both exact),
@@ -417,12 +430,13 @@ __device__ __forceinline__ uint4 fp6_fetch(const Fp6Args& a, __amdgpu_buffer_rsr
 
 // One wave's K loop: its two slots x TN blocks of 32 columns.
 //
-// What bounds it: on long K the chip's power.  The matrix cores by themselves reach 8.1 POP/s on zeros and 6.1 on weight
-// levels and activation codes, at 1.6 instead of 2.1 GHz; with three vector instructions and half an operand read
-// from LDS to each of them 4.8.  So what a product moves and widens counts as much as what it waits for: work-groups of eight waves
+// What bounds it: on long K the waits of one work-group per compute unit first (8192 x 4096 x 8192 on zero operands 130 us, where
+// the matrix cores by themselves take 66), then the chip's power (the same instructions on weight levels and activation codes 163 us:
+// what changes is the clock).  So what a product moves and widens counts as much as what it waits for: work-groups of eight waves
 // widen a column once per 512 rows.  (512 x 128 / 256 x 128 / 256 x 64 outputs: 8192 x 4096 x 8192 167 / 171 / 217 us; two
 // columns of waves with the weights through LDS, 256 x 256: 186.)  On short K the first reads and the epilogue: 6 us.
-template <int TN, int WM, int WN, bool CONV, bool RAGGED, bool GELU>
+// TWO0, TWO1: the first, the second tile has hi and lo parts for one accumulator (fp6_pair_joined).
+template <int TN, int WM, int WN, bool CONV, bool RAGGED, bool GELU, bool TWO0 = false, bool TWO1 = false>
 __device__ __forceinline__ void fp6_k_loop(const Fp6Args& a, uint8_t* smem, v16f (&acc)[2][TN], const Fp6Pair& pair, int n0) {
   constexpr int NW = WM * WN, NT = LANES * NW, BN = 32 * TN * WN;
   constexpr int PP = BN * 4 / NT;  // 16-byte pieces a thread stages per 128 k
@@ -451,18 +465,22 @@ __device__ __forceinline__ void fp6_k_loop(const Fp6Args& a, uint8_t* smem, v16f
     for (int p = 0; p < PP; ++p) dst[p] = fp6_fetch<CONV, RAGGED>(a, xr, col[p], t);
   };
 
-  const uint32_t part = (uint32_t)a.nsteps * (uint32_t)pair.stride - (pair.two ? FP6_FRAG : 0);
-  constexpr int R = 4;  // K steps of weights in flight
-  Fp6Frag ring[R][2];
-  const __amdgpu_buffer_rsrc_t w0 = fp6_rsrc(a.w + pair.off0, part);
-  const __amdgpu_buffer_rsrc_t w1 = fp6_rsrc(a.w + pair.off1, part);
-  auto load_w = [&](int step, Fp6Frag (&f)[2]) {
+  constexpr bool JOINED = TWO0 || TWO1;
+  constexpr int NA0 = TWO0 ? 2 : 1, NA = NA0 + (TWO1 ? 2 : 1);  // operands a K step, of the first tile and in all
+  constexpr int R = JOINED ? 2 : 4;                             // K steps of weights in flight
+  Fp6Frag ring[R][NA];
+  const int stride0 = JOINED ? NA0 * FP6_FRAG : pair.stride, stride1 = JOINED ? (NA - NA0) * FP6_FRAG : pair.stride;
+  const uint32_t cut = pair.two ? FP6_FRAG : 0;
+  const __amdgpu_buffer_rsrc_t w0 = fp6_rsrc(a.w + pair.off0, (uint32_t)a.nsteps * (uint32_t)stride0 - cut);
+  const __amdgpu_buffer_rsrc_t w1 = fp6_rsrc(a.w + pair.off1, (uint32_t)a.nsteps * (uint32_t)stride1 - cut);
+  auto load_w = [&](int step, Fp6Frag (&f)[NA]) {
     step = step < a.nsteps ? step : a.nsteps - 1;  // past the end: any valid step
-    const int soff = step * pair.stride;
 #pragma unroll
-    for (int i = 0; i < 2; ++i) {
-      const fp6_v4u q = __builtin_amdgcn_raw_buffer_load_b128(i ? w1 : w0, lane * 16, soff, 0);
-      const fp6_v2u d = __builtin_amdgcn_raw_buffer_load_b64(i ? w1 : w0, lane * 8 + 1024, soff, 0);
+    for (int i = 0; i < NA; ++i) {
+      const bool second = i >= NA0;
+      const int soff = second ? step * stride1 + (i - NA0) * FP6_FRAG : step * stride0 + i * FP6_FRAG;
+      const fp6_v4u q = __builtin_amdgcn_raw_buffer_load_b128(second ? w1 : w0, lane * 16, soff, 0);
+      const fp6_v2u d = __builtin_amdgcn_raw_buffer_load_b64(second ? w1 : w0, lane * 8 + 1024, soff, 0);
       f[i].a = (v4i){(int)q.x, (int)q.y, (int)q.z, (int)q.w};
       f[i].b = (v2i){(int)d.x, (int)d.y};
     }
@@ -477,7 +495,7 @@ __device__ __forceinline__ void fp6_k_loop(const Fp6Args& a, uint8_t* smem, v16f
   load_w(0, ring[0]), load_w(1, ring[1]);
   __builtin_amdgcn_sched_barrier(0);
   fetch(2, raw[0]);
-  load_w(2, ring[2]), load_w(3, ring[3]);
+  if constexpr (R == 4) load_w(2, ring[2]), load_w(3, ring[R - 1]);
   __builtin_amdgcn_sched_barrier(0);
   const float bias = fp6_stage_meta(a, pair, row, meta, lane);
   if (GELU && wave == 0) fp6_stage_bins(a.bins, (v2u*)(stage + 2 * BUF), lane);
@@ -529,13 +547,15 @@ __device__ __forceinline__ void fp6_k_loop(const Fp6Args& a, uint8_t* smem, v16f
     constexpr int P = decltype(parity_tag)::value;
     auto step = [&](auto u_tag) {
       constexpr int u = decltype(u_tag)::value;
-      const Fp6Frag (&w)[2] = ring[(2 * P + u) % R];
+      const Fp6Frag (&w)[NA] = ring[(2 * P + u) % R];
       // the step after this one: in the same chunk, or in the next, which is in LDS once all waves have passed the barrier
       constexpr int NP = u ? 1 - P : P, NU = 1 - u;
       constexpr int BARRIER = u ? TN / 2 : 0;  // multiplied before the barrier, whose wait they hide
       auto multiply = [&](int j) {
-        acc[0][j] = fp6_mfma(w[0], b[j], acc[0][j]);
-        acc[1][j] = fp6_mfma(w[1], b[j], acc[1][j]);
+        if constexpr (TWO0) acc[0][j] = fp6_mfma_hi(w[0], b[j], acc[0][j]);
+        if constexpr (TWO1) acc[1][j] = fp6_mfma_hi(w[NA - 2], b[j], acc[1][j]);
+        acc[0][j] = fp6_mfma(w[NA0 - 1], b[j], acc[0][j]);
+        acc[1][j] = fp6_mfma(w[NA - 1], b[j], acc[1][j]);
       };
       if constexpr (u == 1) {
 #pragma unroll
@@ -603,14 +623,41 @@ __device__ __forceinline__ bool fp6_block(const Fp6Args& a, int* bx, int* by) {
   return *bx < a.gx;
 }
 
+// Sets the grid of a.pairs pairs, `rows` to a work-group, and of its columns, `cols` blocks of 32 to a work-group; -> work-groups.
+// Whichever way of dealing the blocks out to the eight XCDs leaves fewer of them idle: five column blocks of 64 on five
+// XCDs, 4096 x 4096 x 300, took 24.9 us.
+inline int64_t fp6_grid(Fp6Args& a, int cols, int rows) {
+  a.gx = (a.N + 32 * cols - 1) / (32 * cols);
+  a.gy = (a.pairs + rows - 1) / rows;
+  const int64_t by_cols = (int64_t)(a.gx + 7) / 8 * 8 * a.gy, by_rows = (int64_t)(a.gy + 7) / 8 * 8 * a.gx;
+  a.by_rows = by_rows < by_cols;
+  return a.by_rows ? by_rows : by_cols;
+}
+
 // (without the bins of GELU output, which lie behind that)
 template <int TN, int WM, int WN>
 constexpr size_t fp6_lds() {
   return (size_t)WM * WN * FP6_META_BYTES + 2 * (size_t)(TN * WN) * 2 * FP6_LDS_FRAG;
 }
 
+// What a wave's two tiles come to.
+template <int TN, int WM, int WN, bool GELU>
+__device__ __forceinline__ void fp6_finish_pair(const Fp6Args& a, const uint8_t* smem, v16f (&acc)[2][TN], const Fp6Pair& pair, int n0) {
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const float* mp = (const float*)smem + wave * (FM_FIELDS * 64) + 16 * (lane >> 5);
+  const int n = n0 + wave / WM * TN * 32 + (lane & 31);
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    const int t = i ? pair.t1 : pair.t0;
+    if (t < 0) break;
+    const int rows = lane_rows(t == a.n_tiles - 1 ? a.last_rows : TILE_M, lane);
+    fp6_finish<TN, GELU>(a, acc[i], mp + i * TILE_M, (const v2u*)(smem + fp6_lds<TN, WM, WN>()), rows, t * TILE_M + 16 * (lane >> 5), n);
+  }
+}
+
 // GELU: out_kind 3, chosen by the host.  An instantiation of its own: beside the other outputs the GELU code cost all of
-// them registers (PLACEHOLDER).
+// them registers (two column blocks a wave: 15 to 18 spilled; 64 x 128 outputs: three waves a SIMD instead of four).
 template <int TN, int WM, int WN, bool CONV, bool RAGGED, bool GELU>
 // (waves per SIMD: what the registers of the K loop leave room for)
 __global__ __launch_bounds__(LANES * WM * WN, TN == 4 || (TN == 2 && WN == 4) ? 2 : TN == 2 || WN > 1 ? 3 : 4) void fp6_tile_kernel(Fp6Args a) {
@@ -632,15 +679,34 @@ __global__ __launch_bounds__(LANES * WM * WN, TN == 4 || (TN == 2 && WN == 4) ? 
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[0][j][r] = __builtin_fmaf(16.0f, acc[0][j][r], acc[1][j][r]);
   }
-  const float* mp = (const float*)smem_raw + wave * (FM_FIELDS * 64) + 16 * (lane >> 5);
-  const int n = n0 + wn * TN * 32 + (lane & 31);
-#pragma unroll
-  for (int i = 0; i < 2; ++i) {
-    const int t = i ? pair.t1 : pair.t0;
-    if (t < 0) break;
-    const int rows = lane_rows(t == a.n_tiles - 1 ? a.last_rows : TILE_M, lane);
-    fp6_finish<TN, GELU>(a, acc[i], mp + i * TILE_M, (const v2u*)(smem_raw + fp6_lds<TN, WM, WN>()), rows, t * TILE_M + 16 * (lane >> 5), n);
-  }
+  fp6_finish_pair<TN, WM, WN, GELU>(a, smem_raw, acc, pair, n0);
+}
+
+// The same with neighbouring tiles in a wave (fp6_pair_joined).  A tile with Fixed-8 rows as a pair by itself is up to one
+// wave's work more than the rows: 256 rows with one such tile are five pairs, and where a work-group has four waves, a second row block
+// that fetches and widens all columns again.  Joined they are four, one of which multiplies half as much again (two such tiles: twice
+// as much) while the others wait: better where work-groups go through the chip in several rounds, worse where each is alone with its chain.
+// 60:35:5, 256 x 128 outputs, by themselves / joined: 256 x 1440 x 100352 (3x3) 55.0 / 37.5 us, 512 x 2304 x 25088 (3x3) 34.3 /
+// 26.6; 256 x 64: 768 x 3072 x 4096 13.0 / 16.1.  (The K loop with three or four operands a step has two steps of weights in flight
+// instead of four, as many registers.)
+template <int TN, int WM, int WN, bool CONV, bool RAGGED>
+__global__ __launch_bounds__(LANES * WM * WN, TN == 2 && WM == 4 ? 3 : 2) void fp6_joined_kernel(Fp6Args a) {
+  extern __shared__ __attribute__((aligned(16))) uint8_t smem_raw[];
+  int bx, by;
+  if (!fp6_block(a, &bx, &by)) return;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int q = by * WM + wave % WM;  // (past the last pair: as above)
+  const Fp6Pair pair = fp6_pair_joined(a, q < a.pairs ? q : a.pairs - 1);
+  const int n0 = bx * (32 * TN * WN);
+  v16f acc[2][TN];
+  // (every way passes the same barriers)
+  if (pair.t0 >= a.n_single)
+    fp6_k_loop<TN, WM, WN, CONV, RAGGED, false, true, true>(a, smem_raw, acc, pair, n0);
+  else if (pair.t1 >= a.n_single)
+    fp6_k_loop<TN, WM, WN, CONV, RAGGED, false, false, true>(a, smem_raw, acc, pair, n0);
+  else
+    fp6_k_loop<TN, WM, WN, CONV, RAGGED, false>(a, smem_raw, acc, pair, n0);
+  if (q < a.pairs) fp6_finish_pair<TN, WM, WN, false>(a, smem_raw, acc, pair, n0);
 }
 
 }  // namespace rmsmp

@@ -15,6 +15,7 @@ SHAPES = list(range(1, 10))
 # the dispatch record of each: the tile kernel's blocks per wave, waves along the rows, along the columns; the split kernels'
 # waves and, on half tiles, blocks of 16 columns
 TILES = {1: (4, 4, 1), 2: (2, 2, 2), 3: (2, 1, 4), 4: (2, 4, 1), 5: (1, 2, 1), 6: (1, 1, 4), 14: (4, 8, 1), 15: (2, 2, 1)}
+TILES_JOINED = {20: (4, 4, 1), 21: (2, 1, 4), 22: (2, 4, 1), 23: (4, 8, 1), 24: (2, 2, 1)}
 SPLITS = {7: (4, 0, 0), 8: (8, 0, 0), 9: (16, 0, 0), 16: (4, 1, 0), 17: (8, 1, 0), 18: (4, 2, 0), 19: (8, 2, 0)}
 
 
@@ -29,7 +30,10 @@ def rm():
 def _ran(rm, shape):
     """The last launch was of the shape that was asked for."""
     kernel, numbers = rm.rmsmp_debug_last_dispatch()
-    assert (kernel, numbers[:3]) == (("fp6_tile", TILES[shape]) if shape in TILES else ("fp6_split", SPLITS[shape]))
+    if shape in TILES_JOINED:
+        assert (kernel, numbers[:3], numbers[3] & 4) == ("fp6_tile", TILES_JOINED[shape], 4)
+    else:
+        assert (kernel, numbers[:3]) == (("fp6_tile", TILES[shape]) if shape in TILES else ("fp6_split", SPLITS[shape]))
 
 
 def _to_dev(a):
@@ -88,7 +92,7 @@ def test_gemm_every_work_group_shape(rm, oracle, shape, M, K, N, ratio):
 
     def call(Y, ep):
         rm.rmsmp_gemm(p, X, N, ep, Y)
-        _ran(rm, shape)
+        _ran(rm, 1 if shape in TILES_JOINED and ep.out_kind == rm.OUT_GELU_U4 else shape)
     rm.rmsmp_debug_set_wave_split(0, shape, 0, 0)
     try:
         _check_outputs(rm, oracle, call, p, M, N, ref, acc, (3 * shape) % 16, bias, shape % 3 == 0)
@@ -134,7 +138,7 @@ def test_conv_every_work_group_shape(rm, oracle, shape, geom, M):
 
     def call(Y, ep):
         rm.rmsmp_conv2d(p, X, d, ep, Y, ws)
-        _ran(rm, shape)
+        _ran(rm, 1 if shape in TILES_JOINED and ep.out_kind == rm.OUT_GELU_U4 else shape)
     rm.rmsmp_debug_set_wave_split(0, shape, 0, 0)
     try:
         _check_outputs(rm, oracle, call, p, M, N, ref, acc, z, bias, shape % 3 == 0)
@@ -147,6 +151,30 @@ def test_conv_every_work_group_shape(rm, oracle, shape, geom, M):
 @pytest.mark.parametrize("geom,M", CONVS)
 def test_conv_further_work_group_shapes(rm, oracle, shape, geom, M):
     test_conv_every_work_group_shape(rm, oracle, shape, geom, M)
+
+
+# neighbouring tiles joined in a wave (even numbers of tiles, Fixed-8 rows, no GELU output): waves of two tiles in one part, of one in
+# two parts, of both; a last row block that is not full, a last tile that is not
+JOINED = [20, 21, 22, 23, 24]
+
+
+@pytest.mark.parametrize("shape", JOINED)
+@pytest.mark.parametrize("M,K,N,ratio", [(64, 576, 256, (35, 60, 5)), (50, 64, 65, (0, 0, 100)), (256, 384, 129, (60, 35, 5)), (246, 130, 133, (0, 60, 40)), (320, 1002, 31, (40, 50, 10)),
+                                         (576, 192, 257, (60, 35, 5)), (1088, 320, 140, (0, 40, 60))])
+def test_gemm_joined_tiles(rm, oracle, shape, M, K, N, ratio):
+    test_gemm_every_work_group_shape(rm, oracle, shape, M, K, N, ratio)
+
+
+@pytest.mark.parametrize("shape", JOINED)
+@pytest.mark.parametrize("geom,M", [c for c in CONVS if (c[1] + 31) // 32 % 2 == 0] + [((2, 64, 15, 13, 3, 3, 1, 1), 256), ((2, 24, 13, 11, 3, 3, 1, 1), 312)])
+def test_conv_joined_tiles(rm, oracle, shape, geom, M):
+    test_conv_every_work_group_shape(rm, oracle, shape, geom, M)
+
+
+@pytest.mark.parametrize("shape", JOINED)
+@pytest.mark.parametrize("scheme_code", [2])
+def test_mixed_sums_just_below_what_fp32_holds_joined_tiles(rm, oracle, scheme_code, shape):
+    test_mixed_sums_just_below_what_fp32_holds(rm, oracle, scheme_code, shape)
 
 
 # the split kernel on half tiles: 4 and 8 waves, 16 and 32 columns; rows that end in a tile's first half, fewer K steps than

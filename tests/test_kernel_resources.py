@@ -59,6 +59,12 @@ def test_fp6_tile_kernels_keep_their_sums_in_registers(kernels):
     assert len(tile) == 8 * 2 * 2 * 2
 
 
+def test_fp6_joined_kernels_keep_their_sums_in_registers(kernels):
+    """The same for the five shapes with neighbouring tiles joined in a wave (blocks, waves, waves, convolution, ragged)."""
+    joined = _named(kernels, "fp6_joined_kernel")
+    assert {a: use for a, use in joined.items() if use[1] != 0} == {} and len(joined) == 5 * 2 * 2
+
+
 def test_lds_resident_kernels_without_a_bias_have_the_registers_their_estimates_assume(kernels):
     """Template arguments: taps, K steps, pixel blocks, K split, side by side, tile pairs, in parts, bias.  With 64 pixels a wave,
     K split and two tile pairs three work-groups share a compute unit (at most 168 registers; 768 channels have always taken
