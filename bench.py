@@ -110,11 +110,11 @@ def kernel_of(rm, layer):
     taps, cpt = layer["k"] * layer["k"], layer["C"] // 32
     flags = tuple("true" if split[3] & bit else "false" for bit in (1, 2))
     if kernel == "lds_resident":
-        return "rmsmp::conv_wide_kernel<%d, %d, %d, %d, %d, %d, false>" % ((taps, cpt) + split)
+        return "rmsmp::conv_wide_kernel<%d, %d, %d, %d, %d, %d, false, false>" % ((taps, cpt) + split)
     if kernel == "fp6_tile":
-        return "rmsmp::fp6_tile_kernel<%d, %d, %d, %s, %s>" % (split[:3] + flags)
+        return ("rmsmp::fp6_joined_kernel<%d, %d, %d, %s, %s>" if split[3] & 4 else "rmsmp::fp6_tile_kernel<%d, %d, %d, %s, %s, false>") % (split[:3] + flags)
     if kernel == "fp6_split":
-        return "rmsmp::fp6_split_kernel<%d, %s, %s>" % (split[:1] + flags)
+        return "rmsmp::fp6_half_kernel<%d, %d, %s, %s>" % (split[:2] + flags) if split[1] else "rmsmp::fp6_split_kernel<%d, %s, %s>" % (split[:1] + flags)
     if kernel == "first_layer":
         return "rmsmp::conv_first_kernel"
     return kernel

@@ -1,7 +1,7 @@
 #!/usr/bin/env python3
 """Times the library on every benchmark configuration (synthetic inputs, one GPU) and prints a table.
 
-    python -m paper_2111_00153_amd.bench_configs [gemm] [conv] [skinny] [sweep] [extra] [qat] [peaks] [cases [NAME ...]] [calib]
+    python -m paper_2111_00153_amd.bench_configs [gemm] [conv] [skinny] [sweep] [extra] [qat] [peaks] [power] [cases [NAME ...]] [calib]
 
 (`calib` adds one plain 256 MiB device-to-device copy: a kernel of known size to scale rocprofv3's
 FETCH_SIZE / WRITE_SIZE readings with when the script runs under the profiler.)
@@ -11,7 +11,8 @@ events; the median block is reported.  Throughput counts 2*M*K*N operations of t
 whatever the row schemes or padding.  The skinny configuration (weights 4096 x 4096, 1..64
 activation columns) is timed twice: "warm" launches the same packed weights every time (they stay
 in the last-level cache), "cold" rotates through enough packed copies (> 512 MB) that every launch
-streams its weights from HBM.  `peaks` prints the machine's own rates, `cases` takes the
+streams its weights from HBM.  `peaks` prints the machine's own rates, `power` one large product on
+drawn and on zero operands (the same instructions: what differs is the clock), `cases` takes the
 listed cases of perf/cases.py, or those named, through 20 passes each (for a profiler).  No oracle is involved here: parity is the tests' job.
 """
 import os
@@ -156,6 +157,23 @@ def qat_kernels():
               % (name, M, K, us, M * K * bpe / us / 1e3, bpe), flush=True)
 
 
+def power():
+    """The largest listed product with its operands as drawn, with zero activations, and with zero weights as well."""
+    M, K, N = 8192, 4096, 8192
+    rng = si.rng_for(7)
+    W = si.weights_rowscaled(rng, M, K)
+    scheme = si.scheme_permutation(rng, rm.rmsmp_ratio_counts(M, 35, 60, 5))
+    alpha = np.abs(W).max(axis=1).astype(np.float32)
+    X = torch.from_numpy(rm.pack_u4(si.act_codes_u4(rng, (N, K)))).to(DEV)
+    Y = torch.empty((N, M // 2), dtype=torch.uint8, device=DEV)
+    ep = rm.make_epilogue(0.05, 0, 4, None, True, rm.OUT_U4, 2.0)
+    for name, w, x in [("drawn operands", W, X), ("zero activations", W, torch.zeros_like(X)), ("zero weights and activations", np.zeros_like(W), torch.zeros_like(X))]:
+        p = rm.rmsmp_pack_weights(w, scheme, alpha=alpha)
+        us = time_launches([rm.gemm_launcher(p, x, N, ep, Y)], iters=100)
+        print("power M%d K%d N%d %-30s: %8.2f us  %8.1f TOPS  %s" % (M, K, N, name, us, 2.0 * M * K * N / us / 1e6, rm.rmsmp_debug_last_dispatch()[0]), flush=True)
+        p.free()
+
+
 def main():
     which = set(sys.argv[1:]) or {"gemm", "conv", "skinny"}
     print("device:", torch.cuda.get_device_name(0), flush=True)
@@ -192,6 +210,8 @@ def main():
             dst = torch.empty_like(src)
             us = time_launches([lambda: dst.copy_(src)], iters=20)
             print("torch copy_, %4d MiB: %.0f GB/s (read + written)" % (mib, 2.0 * (mib << 20) / us / 1e3), flush=True)
+    if "power" in which:
+        power()
     if "cases" in which:
         from perf import cases
         listed = cases.listed()
