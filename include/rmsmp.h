@@ -307,7 +307,7 @@ rmsmp_status rmsmp_ste_backward(const float* W, const float* alpha, const float*
  *   tile kernel, 7, 8, 9 the split kernel with 4, 8, 16 waves (8 and 9 also for the two layers of a pair),
  *   10..13 a work-group shape of the skinny kernel, 14 and 15 two more of the tile kernel, 16..19 the split kernel
  *   on half weight tiles with 4 or 8 waves and 16 (16, 17) or 32 columns (18, 19; also for a pair), 20..24 a shape of the tile
- *   kernel with neighbouring tiles joined in a wave (even numbers of tiles with Fixed-8 rows, no GELU; 1 elsewhere);
+ *   kernel with neighbouring tiles joined in a wave (layers with Fixed-8 rows, no GELU; 1 elsewhere);
  *   side_by_side = 1 instead: the int8 kernels only
  *   (a convolution that needs a workspace is then lowered into it), 2: the general kernel only.
  * rmsmp_debug_last_dispatch -- what the calling thread's last rmsmp_gemm / rmsmp_conv2d /

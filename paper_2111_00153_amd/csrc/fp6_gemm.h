@@ -187,12 +187,13 @@ __device__ __forceinline__ Fp6Pair fp6_pair(const Fp6Args& a, int q) {
   return p;
 }
 
-// The other way to give tiles to waves (fp6_joined_kernel; an even number of tiles): two neighbouring ones to each, whatever they
-// hold.  A tile with Fixed-8 rows is then two operands a K step for one accumulator.
+// The other way to give tiles to waves (fp6_joined_kernel): two neighbouring ones to each, whatever they hold; twice the same one
+// where the last, which has Fixed-8 rows, is left over.  Such a tile is then two operands a K step for one accumulator.
 __device__ __forceinline__ Fp6Pair fp6_pair_joined(const Fp6Args& a, int q) {
   const int64_t one = (int64_t)a.nsteps * FP6_FRAG;
   auto off = [&](int t) { return (t <= a.n_single ? t : 2 * t - a.n_single) * one; };
-  return Fp6Pair{2 * q, 2 * q + 1, false, off(2 * q), off(2 * q + 1), FP6_FRAG};
+  const int t0 = 2 * q, t1 = t0 + 1 < a.n_tiles ? t0 + 1 : -1;
+  return Fp6Pair{t0, t1, false, off(t0), off(t1 < 0 ? t0 : t1), FP6_FRAG};
 }
 
 // Row data of a pair, a row a lane: multiplier rowscale * act_scale * 32, zero point * row sum / 32 (both exact),

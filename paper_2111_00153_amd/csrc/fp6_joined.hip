@@ -10,7 +10,7 @@ template <int TN, int WM, int WN, bool CONV, bool RAGGED>
 static int joined_launch(Fp6Args& a, hipStream_t s) {
   static std::atomic<uint64_t> allowed{0};
   if (const int rc = allow_large_lds((const void*)fp6_joined_kernel<TN, WM, WN, CONV, RAGGED>, allowed)) return rc;
-  a.pairs = a.n_tiles / 2;
+  a.pairs = (a.n_tiles + 1) / 2;
   const int64_t blocks = fp6_grid(a, TN * WN, WM);
   if (blocks > 0x7fffffff) return (int)hipErrorInvalidValue;
   hipLaunchKernelGGL((fp6_joined_kernel<TN, WM, WN, CONV, RAGGED>), dim3((unsigned)blocks), dim3(LANES * WM * WN), (fp6_lds<TN, WM, WN>()), s, a);

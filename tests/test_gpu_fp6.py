@@ -153,20 +153,20 @@ def test_conv_further_work_group_shapes(rm, oracle, shape, geom, M):
     test_conv_every_work_group_shape(rm, oracle, shape, geom, M)
 
 
-# neighbouring tiles joined in a wave (even numbers of tiles, Fixed-8 rows, no GELU output): waves of two tiles in one part, of one in
-# two parts, of both; a last row block that is not full, a last tile that is not
+# neighbouring tiles joined in a wave (Fixed-8 rows, no GELU output): waves of two tiles in one part, of one in two parts, of both, of a
+# tile that is left over; a last row block that is not full, a last tile that is not
 JOINED = [20, 21, 22, 23, 24]
 
 
 @pytest.mark.parametrize("shape", JOINED)
-@pytest.mark.parametrize("M,K,N,ratio", [(64, 576, 256, (35, 60, 5)), (50, 64, 65, (0, 0, 100)), (256, 384, 129, (60, 35, 5)), (246, 130, 133, (0, 60, 40)), (320, 1002, 31, (40, 50, 10)),
+@pytest.mark.parametrize("M,K,N,ratio", [(64, 576, 256, (35, 60, 5)), (50, 64, 65, (0, 0, 100)), (256, 384, 129, (60, 35, 5)), (246, 130, 133, (0, 60, 40)), (320, 1002, 31, (40, 50, 10)), (96, 192, 65, (35, 60, 5)), (18, 330, 40, (0, 0, 100)), (846, 130, 70, (0, 0, 100)),
                                          (576, 192, 257, (60, 35, 5)), (1088, 320, 140, (0, 40, 60))])
 def test_gemm_joined_tiles(rm, oracle, shape, M, K, N, ratio):
     test_gemm_every_work_group_shape(rm, oracle, shape, M, K, N, ratio)
 
 
 @pytest.mark.parametrize("shape", JOINED)
-@pytest.mark.parametrize("geom,M", [c for c in CONVS if (c[1] + 31) // 32 % 2 == 0] + [((2, 64, 15, 13, 3, 3, 1, 1), 256), ((2, 24, 13, 11, 3, 3, 1, 1), 312)])
+@pytest.mark.parametrize("geom,M", CONVS + [((2, 64, 15, 13, 3, 3, 1, 1), 256), ((2, 24, 13, 11, 3, 3, 1, 1), 312)])
 def test_conv_joined_tiles(rm, oracle, shape, geom, M):
     test_conv_every_work_group_shape(rm, oracle, shape, geom, M)
 
