@@ -1,7 +1,7 @@
 #!/usr/bin/env python3
 """Benchmark of the RMSMP hot path on one MI355X.
 
-One step = one pass of the whole hot path over one batch of configs[3]: the 20 convolutions of
+One step = one pass of the whole hot path over one batch: the 20 convolutions of
 ResNet-18 at batch 64 and 224x224 (Section 4.2 / Table 6's workload, 232.1 GOP), each one
 rmsmp_conv2d call -- conv1 with Fixed-8 rows and 8-bit activations, the others with weight rows
 Fixed4:PoT4:Fixed8 = 60:35:5 and unsigned 4-bit activations resident in HBM, fused ReLU + 4-bit
@@ -10,7 +10,8 @@ stage's 1x1 shortcut projection read the same tensor and go out together as one
 rmsmp_conv2d_pair call (17 launches per step).  Prints one JSON line.
 
 Besides the contract fields the line carries: per-layer times, the time share of every kernel
-family, the same step with the batch cut in two halves on two streams, the other configurations (configs[1], configs[2], configs[4] with cold weights), the
+family, the same step with the batch cut in two halves on two streams, the other workloads (a 3x3 layer, a
+transformer's FFN product, a GEMM of few columns with cold weights), the
 measured MFMA-only and stream-copy rates of this machine, and the CPU oracle's rate.
 """
 import argparse
@@ -201,10 +202,10 @@ def time_block(torch, fns, iters, warm, reps=5):
 
 
 def other_configs(rm, si, torch, dev):
-    """configs[1], configs[2] (4-bit and fp32 output) and configs[4] with cold weights, timed as
+    """The 3x3 layer, the FFN product (4-bit and fp32 output) and the GEMM of few columns with cold weights, timed as
     blocks of back-to-back launches between two events (no oracle: parity is the tests' job)."""
     out = {}
-    # configs[1]
+    # 256 to 256 channels, 3x3, 32 x 14 x 14
     c = si.CONFIGS[1]
     rng = si.rng_for(1)
     K = c["C"] * 9
@@ -221,7 +222,7 @@ def other_configs(rm, si, torch, dev):
     out["configs[1] conv 256->256 3x3 batch 32, u4 out"] = dict(us=round(us, 3), tops=round(ops / us / 1e6, 1),
                                                                 frac_of_int8_peak=round(ops / us / 1e6 / INT8_MFMA_PEAK_TOPS, 4))
     p.free()
-    # configs[2]
+    # 3072 x 768 x 4096
     M, K, N = 3072, 768, 4096
     rng = si.rng_for(2)
     W = si.weights_bert(rng, M, K)
@@ -238,7 +239,7 @@ def other_configs(rm, si, torch, dev):
         out["configs[2] BERT FFN-up 3072x768x4096, " + label] = dict(
             us=round(us, 3), tops=round(ops / us / 1e6, 1), frac_of_int8_peak=round(ops / us / 1e6 / INT8_MFMA_PEAK_TOPS, 4))
     p.free()
-    # configs[4]: enough packed copies (> the 256 MB last-level cache) that every launch streams from HBM
+    # 4096 x 4096 by few columns: enough packed copies (> the 256 MB last-level cache) that every launch streams from HBM
     M = K = 4096
     rng = si.rng_for(4)
     W = si.weights_rowscaled(rng, M, K)
