@@ -116,6 +116,8 @@ def kernel_of(rm, layer):
         return ("rmsmp::fp6_joined_kernel<%d, %d, %d, %s, %s>" if split[3] & 4 else "rmsmp::fp6_tile_kernel<%d, %d, %d, %s, %s, false>") % (split[:3] + flags)
     if kernel == "fp6_split":
         return "rmsmp::fp6_half_kernel<%d, %d, %s, %s>" % (split[:2] + flags) if split[1] else "rmsmp::fp6_split_kernel<%d, %s, %s>" % (split[:1] + flags)
+    if kernel == "fp6_patch":
+        return "rmsmp::fp6_patch_kernel<%d, %d, %d, %d, false>" % (split[0], split[1], split[3], split[2])
     if kernel == "first_layer":
         return "rmsmp::conv_first_kernel"
     return kernel
@@ -518,8 +520,9 @@ def main():
             u["launch"]()
             kernel, numbers = rm.rmsmp_debug_last_dispatch()
             if kernel in ("lds_resident_pair", "fp6_split_pair"):
-                u["kernel"] = ("rmsmp::conv_wide_pair_kernel<%d>" % (u["layers"][0]["C"] // 32) if kernel == "lds_resident_pair"
-                               else "rmsmp::fp6_split_pair_kernel<%d>" % numbers[0])
+                u["kernel"] = ("rmsmp::fp6_split_pair_kernel<%d>" % numbers[0] if kernel == "fp6_split_pair"
+                               else "rmsmp::fp6_patch_pair_kernel<%d, %d, %d, %d>" % (numbers[0], numbers[1], numbers[3], numbers[2]) if numbers[0]
+                               else "rmsmp::conv_wide_pair_kernel<%d>" % (u["layers"][0]["C"] // 32))
                 u["us"] = time_block(torch, [u["launch"]], args.layer_iters, 10)
                 a, b = u["layers"]
                 fused[a["name"] + " + " + b["name"]] = dict(us=round(u["us"], 3), one_after_the_other_us=round(a["us"] + b["us"], 3),

@@ -307,7 +307,8 @@ rmsmp_status rmsmp_ste_backward(const float* W, const float* alpha, const float*
  *   tile kernel, 7, 8, 9 the split kernel with 4, 8, 16 waves (8 and 9 also for the two layers of a pair),
  *   10..13 a work-group shape of the skinny kernel, 14 and 15 two more of the tile kernel, 16..19 the split kernel
  *   on half weight tiles with 4 or 8 waves and 16 (16, 17) or 32 columns (18, 19; also for a pair), 20..24 a shape of the tile
- *   kernel with neighbouring tiles joined in a wave (layers with Fixed-8 rows, no GELU; 1 elsewhere);
+ *   kernel with neighbouring tiles joined in a wave (layers with Fixed-8 rows, no GELU; 1 elsewhere), 32..41 a shape of
+ *   the patch kernel (convolutions of several taps that it fits, no GELU; the automatic choice elsewhere; 32..34 also for a pair);
  *   side_by_side = 1 instead: the int8 kernels only
  *   (a convolution that needs a workspace is then lowered into it), 2: the general kernel only.
  * rmsmp_debug_last_dispatch -- what the calling thread's last rmsmp_gemm / rmsmp_conv2d /
@@ -315,11 +316,12 @@ rmsmp_status rmsmp_ste_backward(const float* W, const float* alpha, const float*
  *   out (HOST, 5 entries) = {kernel, a, b, c, d} with kernel
  *   0 none, 1 general, 2 skinny (N <= 64), 3 small-channel rows, 4 first layer (3 channels, stride 2),
  *   5 LDS-resident: a, b, c, d = pixel_blocks, k_split, side_by_side, tile_pairs,
- *   6 LDS-resident with two layers in one launch (rmsmp_conv2d_pair),
+ *   6 LDS-resident with two layers in one launch (rmsmp_conv2d_pair): zeros (int8), or as 11 (FP6 patch),
  *   7 FP6 tile: 32-column blocks per wave, waves along the rows, waves along the columns, variant,
  *   8 FP6 split: waves, blocks of 16 columns of a half tile's work-group (0: whole tiles, 32 columns), 0, variant,
  *   9 FP6 split with two layers in one launch: as 8,
- *   10 split on int8 instructions (8-bit activations): as 8;
+ *   10 split on int8 instructions (8-bit activations): as 8,
+ *   11 FP6 patch: 32-column blocks per wave, K split, waves along the columns, pairs of tiles;
  *   variant: 1 for a convolution, plus 2 where a column (pixel) is no multiple of 16 bytes, plus 4 where tiles are joined.  What
  *   is not named is 0.
  * Errors: EINVAL (negative value, NULL).

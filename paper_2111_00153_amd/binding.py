@@ -319,7 +319,7 @@ def rmsmp_debug_set_wave_split(pixel_blocks=0, k_split=0, side_by_side=0, tile_p
 
 
 KERNEL_NAMES = ("none", "general", "skinny", "rows", "first_layer", "lds_resident", "lds_resident_pair", "fp6_tile", "fp6_split", "fp6_split_pair",
-                "int8_split")
+                "int8_split", "fp6_patch")
 
 
 def rmsmp_debug_last_dispatch():

@@ -12,8 +12,8 @@ OBJ_DIR = os.path.join(HERE, "_build")
 # marshalling of the calls a loop makes for every layer: host code on torch's C++ headers and the interpreter's
 PYCALL = os.path.join(HERE, "_pycall.so")
 PYCALL_SOURCE = "csrc/pycall.cpp"
-SOURCES = ["csrc/pack_host.cpp", "csrc/gelu_host.cpp", "csrc/kernels.hip", "csrc/patch_wide.hip", "csrc/conv_first.hip", "csrc/fp6_gemm.hip", "csrc/fp6_joined.hip", "csrc/fp6_split.hip", "csrc/fp6_half.hip", "csrc/i8_split.hip", "csrc/skinny.hip", "csrc/fakequant.hip", "csrc/peaks.hip", "csrc/api.hip"]
-HEADERS = ["csrc/rmsmp_internal.h", "csrc/device_common.h", "csrc/phase_stamps.h", "csrc/patch_wide.h", "csrc/fp6_gemm.h", "csrc/fp6_plan.h", "csrc/split_common.h", "../include/rmsmp.h"]
+SOURCES = ["csrc/pack_host.cpp", "csrc/gelu_host.cpp", "csrc/kernels.hip", "csrc/patch_wide.hip", "csrc/conv_first.hip", "csrc/fp6_gemm.hip", "csrc/fp6_joined.hip", "csrc/fp6_split.hip", "csrc/fp6_half.hip", "csrc/fp6_patch.hip", "csrc/fp6_patch_pair.hip", "csrc/i8_split.hip", "csrc/skinny.hip", "csrc/fakequant.hip", "csrc/peaks.hip", "csrc/api.hip"]
+HEADERS = ["csrc/rmsmp_internal.h", "csrc/device_common.h", "csrc/phase_stamps.h", "csrc/patch_wide.h", "csrc/fp6_gemm.h", "csrc/fp6_patch.h", "csrc/fp6_plan.h", "csrc/split_common.h", "../include/rmsmp.h"]
 # (filter taps, channels / 32) families of the wide LDS-resident kernel: csrc/patch_wide_inst.hip is
 # compiled once per family so that they build in parallel
 WIDE_FAMILIES = [(9, 2), (9, 4), (9, 8), (9, 16), (1, 2), (1, 4), (1, 8), (1, 16), (1, 24)]

@@ -4,6 +4,7 @@
 
 #include <algorithm>
 #include <cmath>
+#include <limits>
 
 #include "patch_wide.h"
 
@@ -271,26 +272,37 @@ int try_launch_wide(const GemmArgs& a, void* stream, float limit_us, bool* appli
   return launch_wide(plan, (hipStream_t)stream);
 }
 
-// Two layers on the same input as one launch (see conv_wide_pair_kernel): a 3x3 layer and a 1x1
+// What the two-layer launch takes, in us: 101 stage heads of 64, 128 and 256 channels (7 to 17 us) within about 15 %; with biases
+// the general epilogue is 1.6 us longer.  (per_unit: of the 3x3 layer's work-groups.)
+static float wide_pair_us(int cpt, const WidePlan& a, bool bias) {
+  const float per_unit = (float)a.blocks / 256.0f;
+  const float us = cpt == 2 ? 7.9f + 5.3f * std::max(0.0f, per_unit - 0.65f) : cpt == 4 ? 7.3f + 2.5f * per_unit : 6.2f + 8.0f * per_unit;
+  return us + (bias ? 1.6f : 0.0f);
+}
+
+// Two layers on the same input as one launch (see conv_wide_pair_kernel): a 3x3 and a 1x1
 // layer with the same 64, 128 or 256 input channels, both with 4-bit activations, neither with
-// the GELU epilogue, each fitting the split the pair kernel is built with.  *applied says whether
+// the GELU epilogue: the FP6 kernels where they are faster, which take images of odd sizes too, or this one where both layers fit the
+// split the pair kernel is built with.  *applied says whether
 // the launch happened; if not, the caller launches the layers one after the other.
 int try_launch_wide_pair(const GemmCall& a0, const GemmCall& b0, void* stream, bool* applied) {
   *applied = false;
-  GemmArgs a, b;
-  int cca = 0, ccb = 0;
   if (a0.X != b0.X || !a0.conv || !b0.conv || forced_general()) return 0;
   if (a0.ep.out_kind == 3 || b0.ep.out_kind == 3) return 0;
-  if (!wide_layer_fits(a0, &a, &cca) || !wide_layer_fits(b0, &b, &ccb)) return 0;
-  if (a.d.KH * a.d.KW != 9 || b.d.KH * b.d.KW != 1) return 0;
-  if (a.d.C != b.d.C || cca != a.d.C || ccb != b.d.C) return 0;
-  const int cpt = a.d.C / KSTEP;
-  if (cpt != 2 && cpt != 4 && cpt != 8) return 0;
-  const WidePairSplit sp = wide_pair_split(cpt);
+  if (a0.d.KH != 3 || a0.d.KW != 3 || b0.d.KH * b0.d.KW != 1 || a0.d.C != b0.d.C) return 0;
+  const int cpt = a0.d.C / KSTEP;
+  if (a0.d.C % KSTEP != 0 || (cpt != 2 && cpt != 4 && cpt != 8)) return 0;
+  GemmArgs a, b;
   WidePlan pa, pb;
-  const bool fits = (a.w.n_tiles + 1) / 2 >= sp.ma && (b.w.n_tiles + 1) / 2 >= sp.mb && wide_plan_mode(a, cca, sp.xa, sp.ka, sp.na, sp.ma, &pa) &&
-                    wide_plan_mode(b, ccb, sp.xb, sp.kb, sp.nb, sp.mb, &pb) && (uint64_t)pa.blocks + pb.blocks <= 0x7fffffffu;
-  if (const int rc = try_launch_fp6_pair(a0, b0, fits, stream, applied); rc != 0 || *applied) return rc;
+  int cca = 0, ccb = 0;
+  bool fits = wide_layer_fits(a0, &a, &cca) && wide_layer_fits(b0, &b, &ccb) && cca == a.d.C && ccb == b.d.C;
+  if (fits) {
+    const WidePairSplit sp = wide_pair_split(cpt);
+    fits = (a.w.n_tiles + 1) / 2 >= sp.ma && (b.w.n_tiles + 1) / 2 >= sp.mb && wide_plan_mode(a, cca, sp.xa, sp.ka, sp.na, sp.ma, &pa) &&
+           wide_plan_mode(b, ccb, sp.xb, sp.kb, sp.nb, sp.mb, &pb) && (uint64_t)pa.blocks + pb.blocks <= 0x7fffffffu;
+  }
+  const float int8_us = fits ? wide_pair_us(cpt, pa, a0.ep.bias || b0.ep.bias) : std::numeric_limits<float>::infinity();
+  if (const int rc = try_launch_fp6_pair(a0, b0, int8_us, stream, applied); rc != 0 || *applied) return rc;
   if (!fits) return 0;
   *applied = true;
   last_dispatch() = DispatchRecord{DK_LDS_RESIDENT_PAIR};

@@ -210,12 +210,13 @@ int launch_ste_backward(const SteArgs& a, void* stream);
 // last_dispatch(): which kernel the calling thread's last call of the library went to; whoever launches writes all of it.
 enum DispatchKernel {
   DK_NONE = 0, DK_GENERAL = 1, DK_SKINNY = 2, DK_ROWS = 3, DK_FIRST_LAYER = 4, DK_LDS_RESIDENT = 5, DK_LDS_RESIDENT_PAIR = 6,
-  DK_FP6_TILE = 7, DK_FP6_SPLIT = 8, DK_FP6_SPLIT_PAIR = 9, DK_INT8_SPLIT = 10
+  DK_FP6_TILE = 7, DK_FP6_SPLIT = 8, DK_FP6_SPLIT_PAIR = 9, DK_INT8_SPLIT = 10, DK_FP6_PATCH = 11
 };
 struct DispatchRecord {
   int kernel = DK_NONE;
   // LDS-resident: the wave split.  FP6 tile: column blocks per wave, waves along the rows, waves along the columns,
-  // kernel variant (1 convolution + 2 ragged columns).  Split kernels: waves, 0, 0, variant.
+  // kernel variant (1 convolution + 2 ragged columns).  Split kernels: waves, 0, 0, variant.  FP6 patch: column blocks per wave, K split,
+  // waves along the columns, pairs of tiles; LDS-resident pair: the same where that kernel runs it, else zeros.
   int xb = 0, ks = 0, nwt = 0, ms = 0;
 };
 int* forced_split();
@@ -234,9 +235,9 @@ int try_launch_wide_pair(const GemmCall& a, const GemmCall& b, void* stream, boo
 int try_launch_fp6(const GemmCall& a, void* stream, bool* applied);
 // Those or the LDS-resident kernel, whichever is estimated to be faster.
 int try_launch_tiled(const GemmCall& a, void* stream, bool* applied);
-// Two convolutions that are small enough for it, as one launch of the FP6 split kernel.  int8_pair: whether the LDS-resident
-// kernel would take both as one launch.
-int try_launch_fp6_pair(const GemmCall& a, const GemmCall& b, bool int8_pair, void* stream, bool* applied);
+// Two convolutions on one input as one launch of the FP6 split kernel or the patch kernel, where that is estimated to be faster
+// than the LDS-resident kernel, which takes int8_us (infinity: it does not take both), or than two launches.
+int try_launch_fp6_pair(const GemmCall& a, const GemmCall& b, float int8_us, void* stream, bool* applied);
 // Skinny kernel (skinny.hip).
 int try_launch_skinny(const GemmArgs& a, void* stream, bool* applied);
 // Split kernel on int8 instructions (i8_split.hip).

@@ -194,6 +194,47 @@ def test_conv_half_tiles(rm, oracle, shape, geom, M):
     test_conv_every_work_group_shape(rm, oracle, shape, geom, M)
 
 
+# the patch kernel: column blocks per wave, K split, waves along the columns, pairs of tiles
+PATCHES = {32: (2, 1, 2, 2), 33: (2, 2, 1, 2), 34: (2, 4, 1, 2), 35: (4, 1, 4, 1), 36: (2, 1, 4, 1), 37: (4, 2, 1, 2), 38: (4, 4, 1, 1), 39: (4, 1, 1, 4), 40: (4, 2, 2, 2),
+           41: (2, 2, 1, 4)}
+
+
+# ragged channel counts, strides (odd sides too: the next image begins before the row's end), no padding, non-square, even and
+# large filters, images that straddle work-groups, more K steps than waves share and fewer; tiles in one part, in two, left over of either kind
+@pytest.mark.parametrize("shape", sorted(PATCHES))
+@pytest.mark.parametrize("geom,M,ratio", [((2, 24, 13, 11, 3, 3, 1, 1), 144, (35, 60, 5)), ((3, 26, 12, 10, 3, 3, 2, 1), 70, (0, 100, 0)), ((3, 32, 13, 11, 3, 3, 2, 1), 128, (60, 35, 5)),
+                                          ((2, 6, 9, 9, 5, 5, 2, 2), 40, (0, 40, 60)), ((1, 22, 11, 9, 2, 4, 3, 1), 64, (35, 60, 5)), ((9, 96, 5, 5, 3, 3, 1, 0), 226, (0, 0, 100)),
+                                          ((1, 64, 15, 17, 3, 3, 1, 1), 64, (35, 60, 5)), ((2, 34, 9, 10, 5, 6, 1, 2), 290, (40, 50, 10)), ((1, 160, 24, 23, 3, 3, 1, 1), 64, (100, 0, 0))])
+def test_conv_patch_kernel(rm, oracle, shape, geom, M, ratio):
+    B, C, H, Wd, KH, KW, stride, pad = geom
+    rng = np.random.default_rng(sum(geom) + M)
+    W = si.weights_rowscaled(rng, M, C * KH * KW)
+    scheme = si.scheme_permutation(rng, rm.rmsmp_ratio_counts(M, *ratio))
+    x = si.act_codes_u4(rng, (B, H, Wd, C))
+    bias = rng.normal(0.0, 0.3, M).astype(np.float32) if shape % 2 else None
+    od = oracle.conv_desc(*geom)
+    OH, OW = oracle.conv_out_hw(od)
+    z = (5 * shape) % 16
+    ref = oracle.quantize_rows(W, scheme)
+    acc = oracle.conv_acc(ref["wint"].reshape(M, C, KH, KW), x.astype(np.int32), od, zpad=z)
+    p = rm.rmsmp_pack_weights(W, scheme, taps=KH * KW)
+    d = rm.ConvDesc(*geom)
+    X = _to_dev(rm.pack_u4(x))
+    need = rm.rmsmp_conv2d_workspace_size(p, d, 4)
+    ws = torch.empty((need,), dtype=torch.uint8, device=DEV) if need else None
+
+    def call(Y, ep):
+        rm.rmsmp_conv2d(p, X, d, ep, Y, ws)
+        if ep.out_kind != rm.OUT_GELU_U4:  # (which this kernel does not have)
+            assert rm.rmsmp_debug_last_dispatch() == ("fp6_patch", PATCHES[shape])
+    rm.rmsmp_debug_set_wave_split(0, shape, 0, 0)
+    try:
+        _check_outputs(rm, oracle, call, p, M, B * OH * OW, ref, acc, z, bias, shape % 3 == 0)
+    finally:
+        rm.rmsmp_debug_set_wave_split(0, 0, 0, 0)
+        p.free()
+
+
 @pytest.mark.parametrize("shape", HALVES)
 @pytest.mark.parametrize("scheme_code", [1, 2])
 def test_mixed_sums_just_below_what_fp32_holds_half_tiles(rm, oracle, scheme_code, shape):

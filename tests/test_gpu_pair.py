@@ -133,6 +133,25 @@ def test_pair_on_half_tiles(rm, oracle, C, MA, MB, H, W, shape):
     Bl.p.free()
 
 
+@pytest.mark.parametrize("shape", [32, 33, 34])
+@pytest.mark.parametrize("C,MA,MB,H,W", [(64, 100, 128, 20, 18), (128, 250, 72, 15, 13), (256, 130, 96, 11, 12)])
+def test_pair_on_the_patch_kernel(rm, oracle, C, MA, MB, H, W, shape):
+    """Both layers as one launch of it, images of even and odd sides."""
+    X, A, Bl = _pair(rm, oracle, 1200 + C, 3, C, H, W, MA, MB, 2, 3)
+    _run_all_kinds(rm, X, A, Bl, 3, "lds_resident_pair", (0, shape, 0, 0))
+    assert rm.rmsmp_debug_last_dispatch()[1] == {32: (2, 1, 2, 2), 33: (2, 2, 1, 2), 34: (2, 4, 1, 2)}[shape]
+    A.p.free()
+    Bl.p.free()
+
+
+def test_pair_with_odd_sides_is_one_launch(rm, oracle):
+    """Small enough for half tiles; the int8 two-layer launch does not take such images."""
+    X, A, Bl = _pair(rm, oracle, 78, 2, 128, 15, 13, 96, 96, 2, 5)
+    _run_all_kinds(rm, X, A, Bl, 5, "fp6_split_pair", (0, 0, 0, 0))
+    A.p.free()
+    Bl.p.free()
+
+
 def test_pair_of_resnet_stage_head_shapes(rm, oracle):
     """layer3.0 of ResNet-18 at a small batch (128 -> 256 channels, 28x28 -> 14x14), zero point 0,
     no bias, ReLU on the 3x3 layer only: the configuration bench.py launches."""
