@@ -6,6 +6,8 @@
 // Both are streaming kernels: 8 bytes per weight for the forward, 8 or 12 for the backward.  gfx950 only.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+
 #include "rmsmp_internal.h"
 
 namespace rmsmp {
@@ -80,7 +82,8 @@ __device__ __forceinline__ float4 project_one(const float4& w, const RowScale& s
 __device__ __forceinline__ float abs_max(float v) { return fabsf(v); }
 __device__ __forceinline__ float abs_max(const float4& v) { return fmaxf(fmaxf(fabsf(v.x), fabsf(v.y)), fmaxf(fabsf(v.z), fabsf(v.w))); }
 
-// max over the T threads of a row; every one gets the result
+// max over the T threads of a row; every one gets the result.  red: an entry per wave of the work-group, all of whose threads
+// come here.
 template <int T>
 __device__ __forceinline__ float row_max(float v, float* red) {
 #pragma unroll
@@ -88,6 +91,7 @@ __device__ __forceinline__ float row_max(float v, float* red) {
   if (T == 64) return v;
   if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
   __syncthreads();
+  red += threadIdx.x / T * (T / 64);
   float m = red[0];
 #pragma unroll
   for (int i = 1; i < T / 64; ++i) m = fmaxf(m, red[i]);
@@ -103,13 +107,18 @@ __device__ __forceinline__ void stream_out(float4* p, const float4& v) {
 }
 
 // A row is read once, all of it at a time, by T threads that hold NV elements (float, or float4 where rows are 16-byte
-// aligned) each; T = 64: four rows per work-group, no barrier.
+// aligned) each; T = 64: four rows per work-group, no barrier; T = 128: two.
+// held_spread: a work-group's rows are eight apart, so that row r is read on XCD r % 8, whose L2 then has it when the backward, a
+// work-group per row, reads it again (3072 x 768, clipped, projection and backward: 10.1 us with neighbouring rows).
+constexpr int held_spread(int T, int NV) { return T == 128 || (T == 64 && NV > 2) ? 8 : 1; }
 template <class V, int T, int NV>
 __global__ __launch_bounds__(T < FQ_THREADS ? FQ_THREADS : T) void fake_quant_held_kernel(FakeQuantArgs a, int nv) {
-  __shared__ float red[T / 64];
+  __shared__ float red[(T < FQ_THREADS ? FQ_THREADS : T) / 64];
   constexpr int ROWS = T < FQ_THREADS ? FQ_THREADS / T : 1;
-  const int64_t r = (int64_t)blockIdx.x * ROWS + (ROWS > 1 ? __builtin_amdgcn_readfirstlane(threadIdx.x / T) : 0);
-  if (r >= a.M) return;
+  constexpr unsigned SPREAD = held_spread(T, NV);
+  const int64_t row = (int64_t)(blockIdx.x / SPREAD) * (SPREAD * ROWS) + blockIdx.x % SPREAD + (ROWS > 1 ? SPREAD * __builtin_amdgcn_readfirstlane(threadIdx.x / T) : 0);
+  if (T == 64 && row >= a.M) return;
+  const int64_t r = row < a.M ? row : a.M - 1;  // (there is a barrier: past the last row that one's maximum once more)
   const V* w = (const V*)(a.W + r * a.K);
   V* out = (V*)(a.What + r * a.K);
   const int tid = threadIdx.x % T;
@@ -127,6 +136,7 @@ __global__ __launch_bounds__(T < FQ_THREADS ? FQ_THREADS : T) void fake_quant_he
     alpha = row_max<T>(m, red);
     if (alpha == 0.0f) alpha = 1.0f;
   }
+  if (row >= a.M) return;
   if (a.alpha_out && tid == 0) a.alpha_out[r] = alpha;
   const RowScale s = row_scale(alpha, scheme);
   if (s.range) {
@@ -243,26 +253,39 @@ bool aligned16(const void* p) { return ((uintptr_t)p & 15) == 0; }
 
 template <class V, int T, int NV>
 void held(const FakeQuantArgs& a, int nv, hipStream_t s) {
-  constexpr int ROWS = T < FQ_THREADS ? FQ_THREADS / T : 1;
-  hipLaunchKernelGGL((fake_quant_held_kernel<V, T, NV>), dim3((unsigned)((a.M + ROWS - 1) / ROWS)), dim3(T < FQ_THREADS ? FQ_THREADS : T), 0, s, a, nv);
+  constexpr int SPREAD = held_spread(T, NV), ROWS = (T < FQ_THREADS ? FQ_THREADS / T : 1) * SPREAD;
+  hipLaunchKernelGGL((fake_quant_held_kernel<V, T, NV>), dim3((unsigned)((a.M + ROWS - 1) / ROWS * SPREAD)), dim3(T < FQ_THREADS ? FQ_THREADS : T), 0, s, a, nv);
 }
 
-// A wave per row of up to 64 elements (128 where there are rows enough to fill the chip with a quarter of the work-groups), a
-// work-group of 256 threads above, of 1024 where rows are long, or few of them are all there is; rows longer than a
-// work-group's registers hold are read twice.  us with tensors out of the cache, row maximum found / alpha given, against a
-// work-group of 256 per row throughout, which divided, and read twice what was not 16-byte aligned:
-//   16384 x 100    7.6 /  7.0, was 20.8 / 14.1     3072 x 769   6.9 / 6.5, was 10.6 / 9.8
-//    4096 x 2000  13.4 / 12.9, was 17.3 / 16.9     3072 x 768   6.7 / 6.0, was  8.2 / 7.4
+// How many threads a row gets.  What bounds these calls besides the bytes is the number of waves that have to be launched, 12 000 of
+// them for 3072 rows of 768 by work-groups of 256, a quarter of whose lanes have nothing to do: with rows enough to fill the
+// chip a wave or two per row, with several elements a lane, take less.  us, tensors in the caches, row maximum found / alpha given, 256 threads per row (the kernel
+// that had these rows before) against:
+//   one wave      6000 x 600   9.1 / 7.3 -> 5.8 / 5.3    16384 x 201  14.5 / 9.8 -> 6.6 / 6.1    4096 x 301  6.1 / 4.6 -> 4.2 / 3.8
+//   two waves     3072 x 768   5.8 / 4.8 -> 4.5 / 3.9     8192 x 1000 14.0 / 11.0 -> 10.4 / 10.3  2048 x 1200 5.4 / 4.1 -> 4.6 / 4.1
+//                 4096 x 1536  9.0 / 7.4 -> 6.9 / 6.3     3072 x 769   6.1 / 4.6 -> 5.0 / 4.7
+//   four waves, two elements a lane: 8192 x 1200 16.0 / 13.7 -> 13.6 / 13.5 (two waves 13.6 / 13.2), 16384 x 2048 38.9 / 38.7 -> 38.2 / 38.7 (two 41.5 / 41.5)
+// Below: 1024 x 768 3.5 / 3.1 with 256 threads, 3.6 / 3.2 with two waves, 3.7 / 3.5 with one.  Work-groups of 1024 where rows are long, or few of
+// them are all there is; rows longer than a work-group's registers hold are read twice.
 template <class V>
 void fake_quant_any(const FakeQuantArgs& a, int64_t nv, hipStream_t s) {
-  if (nv <= 64) held<V, 64, 1>(a, (int)nv, s);
-  else if (nv <= 128 && a.M >= 2048) held<V, 64, 2>(a, (int)nv, s);
-  else if (nv <= 256) held<V, 256, 1>(a, (int)nv, s);
-  else if (nv <= 1024) held<V, 256, 4>(a, (int)nv, s);
-  else if (nv <= 2048 && a.M >= 1024) held<V, 256, 8>(a, (int)nv, s);
-  else if (nv <= 2048) held<V, 1024, 2>(a, (int)nv, s);
-  else if (nv <= 4096 && a.M >= 1024) held<V, 256, 16>(a, (int)nv, s);
-  else if (nv <= 8192) held<V, 1024, 8>(a, (int)nv, s);
+  constexpr bool ONE = sizeof(V) == sizeof(float);  // (rows that are no multiple of 16 bytes)
+  const int n = (int)std::min<int64_t>(nv, 0x7fffffff);
+  if (n <= 64) held<V, 64, 1>(a, n, s);
+  else if (n <= 128 && a.M >= 2048) held<V, 64, 2>(a, n, s);
+  else if (!ONE && n <= 192 && a.M >= 4096) held<V, 64, 3>(a, n, s);
+  else if (ONE && n <= 256 && a.M >= 4096) held<V, 64, 4>(a, n, s);
+  else if (ONE && n <= 512 && a.M >= 4096) held<V, 64, 8>(a, n, s);
+  else if (n <= 256 && a.M >= 1280) held<V, 128, 2>(a, n, s);
+  else if (n <= 512 && a.M >= 1280 && a.M < 8192) held<V, 128, 4>(a, n, s);
+  else if (n <= 512 && a.M >= 8192) held<V, 256, 2>(a, n, s);
+  else if (ONE && n <= 1024 && a.M >= 2048) held<V, 128, 8>(a, n, s);
+  else if (n <= 256) held<V, 256, 1>(a, n, s);
+  else if (n <= 1024) held<V, 256, 4>(a, n, s);
+  else if (n <= 2048 && a.M >= 1024) held<V, 256, 8>(a, n, s);
+  else if (n <= 2048) held<V, 1024, 2>(a, n, s);
+  else if (n <= 4096 && a.M >= 1024) held<V, 256, 16>(a, n, s);
+  else if (n <= 8192) held<V, 1024, 8>(a, n, s);
   else hipLaunchKernelGGL(fake_quant_long_kernel<V>, dim3((unsigned)a.M), dim3(FQ_THREADS), 0, s, a, nv);
 }
 

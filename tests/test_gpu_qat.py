@@ -71,6 +71,13 @@ def test_projection_and_its_backward_at_every_row_length(rm, oracle, M, K):
         assert np.array_equal(dW.cpu().numpy(), G if alpha is None else np.where(np.abs(W) > alpha[:, None], np.float32(0), G))
 
 
+# rows enough for one or two waves a row: the first and last length of each way, numbers of rows that leave a work-group half empty
+@pytest.mark.parametrize("M,K", [(1280, 260), (1281, 1024), (1281, 1028), (1283, 2048), (1281, 257), (1281, 512), (1283, 513), (2049, 1023), (2049, 510), (4096, 516), (4097, 768),
+                                 (4097, 772), (4097, 129), (4099, 255), (4097, 257), (4101, 511), (8191, 1028), (8192, 1028), (8193, 2048)])
+def test_projection_and_its_backward_of_many_rows(rm, oracle, M, K):
+    test_projection_and_its_backward_at_every_row_length(rm, oracle, M, K)
+
+
 def test_fake_quant_equals_what_the_packed_path_multiplies_with(rm, oracle):
     """The projected fp32 weight is rowscale * the integer the packed blob holds."""
     rng = np.random.default_rng(9)
