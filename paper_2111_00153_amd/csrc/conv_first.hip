@@ -59,6 +59,8 @@ __global__ __launch_bounds__(256, 3) void conv_first_kernel(GemmArgs a, FirstGeo
   constexpr int BUF = PH * CF_ROWB;          // bytes per staging buffer
   constexpr int NUNIT = PH * CF_UNITS;
   constexpr int UPT = (NUNIT + 255) / 256;   // units per thread
+  constexpr int ID = KHW * 4 + MODE_;
+  const unsigned touched = touch_kernel<ID, 4>();
   const EpArgs ea = pin_epilogue_args(a);
   const int tid = threadIdx.x;
   const int lane = tid & 63;
@@ -228,6 +230,7 @@ __global__ __launch_bounds__(256, 3) void conv_first_kernel(GemmArgs a, FirstGeo
     TilePos pos = pos0;
     __syncthreads();  // metadata stored / previous pass done with both buffers
     store_units(pos0, raw0, buf0);
+    code_touched(touched);
     __syncthreads();
 
     const int n_rows = mine_live ? lane_rows(tr.nvalid, lane) : 0;
@@ -419,6 +422,7 @@ __global__ __launch_bounds__(256, 3) void conv_first_kernel(GemmArgs a, FirstGeo
     };
     run_tiles(std::integral_constant<int, MODE_>{});
   }
+  code_end<ID>();
 }
 
 static uint32_t cf_div_magic(int64_t d) {

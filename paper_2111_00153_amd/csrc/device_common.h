@@ -13,6 +13,46 @@ namespace rmsmp {
 typedef int v4i __attribute__((ext_vector_type(4)));
 typedef int v16i __attribute__((ext_vector_type(16)));
 
+// ---------------------------------------------------------------- the kernel's own code
+
+// A launch that follows other kernels' finds its code in memory: the instruction cache is empty and what has gone through the L2 since
+// has pushed the code out.  Fetched as it is run it comes line by line, in the way of every wave of the XCD at once; so the
+// first work-groups of each XCD read it as data when they start, all lines at once, and the fetches that follow find it in the L2.
+// For the first layer's and the FP6 patch kernels, between whose launches of a large batch 20 MB and more go through each L2: the stack of a
+// ResNet-18 at batch 64 212.8 -> 210.3 us (in another process 214.7 -> 208.8).  The tile, split, half and skinny kernels did
+// not gain (six GEMMs of an encoder layer at 4096 tokens 54.5 / 54.9, the stack on one image 74.3 / 75.2), and have no such read.
+struct CodeRange {
+  const void* at;
+  uint32_t bytes;
+};
+// From here to code_end<ID>() of the same kernel, which bounds every read; ID: a number of the kernel's own in its translation unit.
+template <int ID>
+__device__ __forceinline__ CodeRange code_here() {
+  uint64_t at;
+  int bytes;
+  asm volatile("s_getpc_b64 %0\n.Lrmsmp_code_%c2:\n\ts_mov_b32 %1, .Lrmsmp_code_end_%c2-.Lrmsmp_code_%c2" : "=s"(at), "=s"(bytes) : "i"(ID));
+  return CodeRange{(const void*)at, (uint32_t)(bytes > 0 ? bytes : 0)};
+}
+template <int ID>
+__device__ __forceinline__ void code_end() {
+  asm volatile(".Lrmsmp_code_end_%c0:" ::"i"(ID));
+}
+// Wave `wave` of the launch's waves on its XCD reads its 8 KB of the code, a dword of each line of 128 bytes.  The result goes to
+// code_touched, behind the wait for a later read.
+__device__ __forceinline__ unsigned touch_code(const CodeRange& c, int wave) {
+  const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(c.at), 0, (int)c.bytes, 0x00020000);
+  const unsigned off = wave < 8 ? (unsigned)wave * 8192u + (threadIdx.x & 63) * 128u : 0x80000000u;
+  const unsigned v = __builtin_amdgcn_raw_buffer_load_b32(r, (int)off, 0, 0);
+  __builtin_amdgcn_sched_barrier(0);
+  return v;
+}
+__device__ __forceinline__ void code_touched(unsigned v) { asm volatile("" ::"v"(v)); }
+// (work-groups go to the eight XCDs in turn)
+template <int ID, int WAVES>
+__device__ __forceinline__ unsigned touch_kernel() {
+  return touch_code(code_here<ID>(), (int)(blockIdx.x >> 3) * WAVES + __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6));
+}
+
 // ---------------------------------------------------------------- operand decode
 
 // Eight two's-complement nibbles per word -> int8 = 16*q, in MFMA slot order.

@@ -270,7 +270,8 @@ __device__ __forceinline__ float patch_wave(const Fp6Args& a, const Fp6Patch& g,
   return bias;
 }
 
-template <int TN, int KS, int WM, int WN, bool RAGGED>
+// ID: see code_here.
+template <int TN, int KS, int WM, int WN, bool RAGGED, int ID>
 __device__ __forceinline__ void patch_body(const PatchFirst& f, const Fp6Args& a, const Fp6Patch& g, const int block) {
   using S = PatchShape<TN, KS, WM, WN>;
   extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
@@ -300,6 +301,7 @@ __device__ __forceinline__ void patch_body(const PatchFirst& f, const Fp6Args& a
 
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const unsigned touched = touch_kernel<ID, S::NW>();
   const int kq = wave % KS, wn = wave / KS % WN, wm = wave / (KS * WN);
   const int q = by * WM + wm;  // (past the last pair: helps to stage the patch)
   const Fp6Pair pair = fp6_pair_joined(a, q < a.pairs ? q : a.pairs - 1);
@@ -320,6 +322,7 @@ __device__ __forceinline__ void patch_body(const PatchFirst& f, const Fp6Args& a
     RMSMP_PATCH_WAVE(2, false, false);
   }
 #undef RMSMP_PATCH_WAVE
+  code_touched(touched);
   float* const meta = (float*)smem + wave * (FM_FIELDS * 64);
   meta[FM_BIAS * 64 + lane] = bias;
 
@@ -385,9 +388,14 @@ __device__ __forceinline__ void patch_body(const PatchFirst& f, const Fp6Args& a
   }
 }
 
+template <int TN, int KS, int WM, int WN>
+constexpr int patch_id() { return ((TN * 8 + KS) * 8 + WM) * 8 + WN; }
+
 template <int TN, int KS, int WM, int WN, bool RAGGED>
 __global__ __launch_bounds__(LANES * KS * WM * WN, 2) void fp6_patch_kernel(FP6_PATCH_FIRST_PARAMS, Fp6Args a, Fp6Patch g) {
-  patch_body<TN, KS, WM, WN, RAGGED>(FP6_PATCH_FIRST_UNPACK(), a, g, (int)blockIdx.x);
+  constexpr int ID = patch_id<TN, KS, WM, WN>() * 2 + (RAGGED ? 1 : 0);
+  patch_body<TN, KS, WM, WN, RAGGED, ID>(FP6_PATCH_FIRST_UNPACK(), a, g, (int)blockIdx.x);
+  code_end<ID>();
 }
 
 // Work-groups of 4 waves where the grid is small or a layer has few rows, of 8 where it has many columns and deep K: of 14 tried on 2 600 layers
