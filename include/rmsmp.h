@@ -308,13 +308,15 @@ rmsmp_status rmsmp_ste_backward(const float* W, const float* alpha, const float*
  *   10..13 a work-group shape of the skinny kernel, 14 and 15 two more of the tile kernel, 16..19 the split kernel
  *   on half weight tiles with 4 or 8 waves and 16 (16, 17) or 32 columns (18, 19; also for a pair), 20..24 a shape of the tile
  *   kernel with neighbouring tiles joined in a wave (layers with Fixed-8 rows, no GELU; 1 elsewhere), 32..41 a shape of
- *   the patch kernel (convolutions of several taps that it fits, no GELU; the automatic choice elsewhere; 32..34 also for a pair);
+ *   the patch kernel (convolutions of several taps that it fits, no GELU; the automatic choice elsewhere; 32..34 also for a pair),
+ *   4, 8 and 16 that many rows of the first-layer kernel's tiles;
  *   side_by_side = 1 instead: the int8 kernels only
  *   (a convolution that needs a workspace is then lowered into it), 2: the general kernel only.
  * rmsmp_debug_last_dispatch -- what the calling thread's last rmsmp_gemm / rmsmp_conv2d /
  *   rmsmp_conv2d_pair ran (a pair that went out as two launches: the second one):
  *   out (HOST, 5 entries) = {kernel, a, b, c, d} with kernel
- *   0 none, 1 general, 2 skinny (N <= 64), 3 small-channel rows, 4 first layer (3 channels, stride 2),
+ *   0 none, 1 general, 2 skinny (N <= 64), 3 small-channel rows,
+ *   4 first layer (3 channels, stride 2): rows of its tiles of output pixels,
  *   5 LDS-resident: a, b, c, d = pixel_blocks, k_split, side_by_side, tile_pairs,
  *   6 LDS-resident with two layers in one launch (rmsmp_conv2d_pair): zeros (int8), or as 11 (FP6 patch),
  *   7 FP6 tile: 32-column blocks per wave, waves along the rows, waves along the columns, variant,

@@ -8,7 +8,8 @@
 //  * Nothing is lowered.  Weights are stored one K step per filter row (element (kh, kw, c) at
 //    kh*32 + kw*4 + c), so a lane's B fragment for filter row kh is four consecutive input pixels
 //    (padded to four bytes each) of input row 2*oh - pad + kh.
-//  * A work-group walks through several 16x16 tiles of output pixels; each wave holds the weights
+//  * A work-group walks through several tiles of output pixels, 16 wide and 4, 8 or 16 high (the rule is at the
+//    launch); each wave holds the weights
 //    of one weight tile in registers the whole time and takes half of the rows of every pixel
 //    tile (the narrower kernel fetched the weights again for every 128 pixels: 14 KiB per wave
 //    against 0.4 KiB of input).  Three work-groups share a compute unit; the launch has exactly
@@ -25,7 +26,7 @@
 //    of its SIMD, and the 4-bit epilogue needs five per output value: convert, two roundings of
 //    the scale product, clamp, pack), so the common case has a loop of its own (template
 //    parameter chosen by the host) that carries nothing else: row multipliers in registers, the
-//    four blocks of a tile in one piece of straight-line code, 4-bit codes stored through a
+//    blocks of a tile in one piece of straight-line code, 4-bit codes stored through a
 //    buffer descriptor whose per-lane offset is fixed for the pass.
 #include <hip/hip_runtime.h>
 
@@ -33,33 +34,36 @@
 
 namespace rmsmp {
 
-constexpr int CF_T = 16;         // output tile: 16 x 16 pixels
+constexpr int CF_T = 16;         // width of an output tile; its largest height
 constexpr int CF_UNITS = 10;     // staged 16-byte units (four pixels each) per input row
 constexpr int CF_ROWB = CF_UNITS * 16;
 constexpr int CF_MAX_TILES = 64;  // row metadata of all weight tiles sits in LDS (512 bytes per tile)
 
 struct FirstGeom {
-  int tiles_w, tiles_h;   // 16x16 output tiles per image
+  int tiles_w, tiles_h;   // output tiles per image
   int total_tiles;        // B * tiles_h * tiles_w
   int tiles_base, tiles_rem;  // work-group i takes tiles_base tiles, one more when i < tiles_rem
-  uint32_t magic_tw;      // ceil(2^32 / tiles_w), 0 when tiles_w == 1
-  uint32_t magic_thw;     // ceil(2^32 / (tiles_w * tiles_h)), 0 when that is 1
+  struct Div {
+    uint32_t magic;  // ceil(2^(32 + shift) / d), 2^shift < d <= 2^(shift + 1); 0 for d == 1
+    int shift;
+  } by_tw, by_thw;   // tiles_w and tiles_w * tiles_h
 };
 
-__device__ __forceinline__ int cf_fast_div(int n, uint32_t magic) {
-  return magic ? (int)__umulhi((uint32_t)n, magic) : n;
-}
+// n / d for 0 <= n < 2^31
+__device__ __forceinline__ int cf_fast_div(int n, const FirstGeom::Div& d) { return d.magic ? (int)(__umulhi((uint32_t)n, d.magic) >> d.shift) : n; }
 
 typedef unsigned cf_v4w __attribute__((ext_vector_type(4)));
 
-template <int KHW, int MODE_>
+// TH: rows of a tile, in blocks of two, TH / 4 of them to each of the two waves that share a weight tile.
+template <int KHW, int TH, int MODE_>
 __global__ __launch_bounds__(256, 3) void conv_first_kernel(GemmArgs a, FirstGeom g) {
   extern __shared__ __attribute__((aligned(16))) uint8_t smem_raw[];
-  constexpr int PH = 2 * (CF_T - 1) + KHW;   // staged input rows per tile
+  constexpr int PH = 2 * (TH - 1) + KHW;     // staged input rows per tile
+  constexpr int NBL = TH / 4;                // blocks of 2 x 16 pixels a wave takes of a tile
   constexpr int BUF = PH * CF_ROWB;          // bytes per staging buffer
   constexpr int NUNIT = PH * CF_UNITS;
   constexpr int UPT = (NUNIT + 255) / 256;   // units per thread
-  constexpr int ID = KHW * 4 + MODE_;
+  constexpr int ID = (KHW * 32 + TH) * 4 + MODE_;
   const unsigned touched = touch_kernel<ID, 4>();
   const EpArgs ea = pin_epilogue_args(a);
   const int tid = threadIdx.x;
@@ -88,11 +92,11 @@ __global__ __launch_bounds__(256, 3) void conv_first_kernel(GemmArgs a, FirstGeo
   };
   auto tile_pos = [&](int t) -> TilePos {
     TilePos p;
-    p.b = cf_fast_div(t, g.magic_thw);
+    p.b = cf_fast_div(t, g.by_thw);
     const int r = t - p.b * (g.tiles_w * g.tiles_h);
-    const int th = cf_fast_div(r, g.magic_tw);
+    const int th = cf_fast_div(r, g.by_tw);
     const int tw = r - th * g.tiles_w;
-    p.oh0 = th * CF_T;
+    p.oh0 = th * TH;
     p.ow0 = tw * CF_T;
     p.ih0 = p.oh0 * 2 - pad;
     // pixel pairs are staged from an odd pixel on; the first staged pixel iw_s + 1 is the last odd
@@ -273,9 +277,9 @@ __global__ __launch_bounds__(256, 3) void conv_first_kernel(GemmArgs a, FirstGeo
         }
         const int s_tile = ((pos.b * a.OH + pos.oh0) * a.OW + pos.ow0) * (int)row_bytes;  // (used by 4-bit stores only)
         const bool col_ok = pos.ow0 + pc < a.OW;
-        // ---- this wave's four blocks (rows 8*(w/2) .. 8*(w/2)+7 of the tile) against its weight tile
+        // ---- this wave's blocks (half of the tile's rows) against its weight tile
         auto do_block = [&](const int bl) {
-          const int oh_l = 8 * (wave >> 1) + 2 * bl + pr;
+          const int oh_l = TH / 2 * (wave >> 1) + 2 * bl + pr;
           const uint8_t* fp = buf + (oh_l * 2) * CF_ROWB + (pc + 2 * hh + pos.shift) * 8;
           v4i bf[KHW];
 #pragma unroll
@@ -334,7 +338,7 @@ __global__ __launch_bounds__(256, 3) void conv_first_kernel(GemmArgs a, FirstGeo
             if (MODE == 1 || whole) {
               // per-lane part of the address fixed for the whole pass, the rest scalar; pixels outside
               // the output get an offset beyond the buffer and are dropped
-              const int s_off = s_tile + (8 * (wave >> 1) + 2 * bl) * s_row;
+              const int s_off = s_tile + (TH / 2 * (wave >> 1) + 2 * bl) * s_row;
               __builtin_amdgcn_raw_buffer_store_b64((v2u){packed[0], packed[1]}, yr, (col_ok && oh < a.OH) ? lane_off : (int)0x80000000, s_off, 0);
             } else if (px_ok) {
               RMSMP_GLOBAL uint8_t* dst = as_global((uint8_t*)ea.Y) + n * row_bytes + (gpos0 >> 1);
@@ -344,14 +348,14 @@ __global__ __launch_bounds__(256, 3) void conv_first_kernel(GemmArgs a, FirstGeo
         };
         // (mine_live is the same for the whole wave: every lane feeds the MFMAs)
         if constexpr (MODE == 1 || MODE == 3) {
-          // All four blocks in one piece of straight-line code, software-pipelined: the MFMA chain of
+          // All blocks of a tile in one piece of straight-line code, software-pipelined: the MFMA chain of
           // block bl + 1 (seven dependent instructions, each waiting for the one before) is issued
           // between the vector instructions that requantize block bl, so the wave's matrix work runs
           // in the shadow of its own vector work (the waves of a SIMD pass the per-tile barrier
           // together and would otherwise all be in their MFMA chains, then all in their epilogues).
           if (mine_live) {
             auto frags = [&](const int bl, v4i (&bf)[KHW]) {
-              const int oh_l = 8 * (wave >> 1) + 2 * bl + pr;
+              const int oh_l = TH / 2 * (wave >> 1) + 2 * bl + pr;
               const uint8_t* fp = buf + (oh_l * 2) * CF_ROWB + (pc + 2 * hh + pos.shift) * 8;
 #pragma unroll
               for (int kh = 0; kh < KHW; ++kh) {
@@ -380,22 +384,22 @@ __global__ __launch_bounds__(256, 3) void conv_first_kernel(GemmArgs a, FirstGeo
                 }
               }
               requant_block<MODE == 3, false>(acc, mkeep, brow, ea.out_inv_scale, packed);
-              const int oh = pos.oh0 + 8 * (wave >> 1) + 2 * bl + pr;
-              const int s_off = s_tile + (8 * (wave >> 1) + 2 * bl) * s_row;
+              const int oh = pos.oh0 + TH / 2 * (wave >> 1) + 2 * bl + pr;
+              const int s_off = s_tile + (TH / 2 * (wave >> 1) + 2 * bl) * s_row;
               __builtin_amdgcn_raw_buffer_store_b64((v2u){packed[0], packed[1]}, yr, (col_ok && oh < a.OH) ? lane_off : (int)0x80000000, s_off, 0);
             };
             v4i bf0[KHW], bf1[KHW];
             frags(0, bf0);
             v16i cur = chain(bf0);
-            frags(1, bf1);
+            if (NBL > 1) frags(1, bf1);
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-            for (int bl = 0; bl < 4; ++bl) {
+            for (int bl = 0; bl < NBL; ++bl) {
               v16i nxt = cur;
-              if (bl + 1 < 4) nxt = chain((bl & 1) ? bf0 : bf1);
-              if (bl + 2 < 4) frags(bl + 2, (bl & 1) ? bf1 : bf0);
+              if (bl + 1 < NBL) nxt = chain((bl & 1) ? bf0 : bf1);
+              if (bl + 2 < NBL) frags(bl + 2, (bl & 1) ? bf1 : bf0);
               finish(bl, cur);
-              if (bl + 1 < 4) {
+              if (bl + 1 < NBL) {
                 // one MFMA of the next block's chain behind every dozen vector instructions of this block's epilogue
 #pragma unroll
                 for (int kh = 0; kh < KHW; ++kh) {
@@ -409,7 +413,7 @@ __global__ __launch_bounds__(256, 3) void conv_first_kernel(GemmArgs a, FirstGeo
           }
         } else {
 #pragma unroll 1
-          for (int bl = 0; bl < 4; ++bl) {
+          for (int bl = 0; bl < NBL; ++bl) {
             if (!mine_live) break;
             do_block(bl);
           }
@@ -425,8 +429,12 @@ __global__ __launch_bounds__(256, 3) void conv_first_kernel(GemmArgs a, FirstGeo
   code_end<ID>();
 }
 
-static uint32_t cf_div_magic(int64_t d) {
-  return d <= 1 ? 0u : (uint32_t)((((uint64_t)1 << 32) + (uint64_t)d - 1) / (uint64_t)d);
+static FirstGeom::Div cf_div_of(int64_t d) {
+  FirstGeom::Div r{0, 0};
+  if (d <= 1) return r;
+  while (((int64_t)2 << r.shift) < d) ++r.shift;
+  r.magic = (uint32_t)((((unsigned __int128)1 << (32 + r.shift)) + (uint64_t)d - 1) / (uint64_t)d);
+  return r;
 }
 
 static bool conv_first_applies(const GemmArgs& a) {
@@ -440,13 +448,13 @@ static bool conv_first_applies(const GemmArgs& a) {
   const int64_t x_bytes = (int64_t)a.d.B * a.d.H * a.d.W * 3;
   if (x_bytes >= ((int64_t)1 << 31) || x_bytes < 16) return false;
   const int64_t tiles = (int64_t)a.d.B * ((a.OH + CF_T - 1) / CF_T) * ((a.OW + CF_T - 1) / CF_T);
-  if (tiles >= ((int64_t)1 << 24)) return false;  // one-multiply division of tile numbers
+  if (tiles >= ((int64_t)1 << 24)) return false;
   return true;
 }
 
-template <int KHW>
+template <int KHW, int TH>
 static int launch_conv_first_t(const GemmArgs& a, const FirstGeom& g, unsigned blocks, hipStream_t s) {
-  constexpr int PH = 2 * (CF_T - 1) + KHW;
+  constexpr int PH = 2 * (TH - 1) + KHW;
   const size_t lds = (size_t)2 * PH * CF_ROWB + (size_t)a.w.n_tiles * TILE_M * (16 + 8);  // at most 12 + 48 KiB
   // which of the four pixel-tile loops the launch needs (see the kernel)
   const int64_t row_bytes = a.M / 2;
@@ -455,24 +463,47 @@ static int launch_conv_first_t(const GemmArgs& a, const FirstGeom& g, unsigned b
   // every lane of the lean loop stores 16 whole codes: full weight tiles, 8-byte aligned places
   const bool all_whole = a.M % TILE_M == 0 && (((uintptr_t)a.Y) & 7) == 0;
   if (u4_plain && a.ep.bias == nullptr && !relu_step && all_whole)
-    hipLaunchKernelGGL((conv_first_kernel<KHW, 1>), dim3(blocks), dim3(256), lds, s, a, g);
+    hipLaunchKernelGGL((conv_first_kernel<KHW, TH, 1>), dim3(blocks), dim3(256), lds, s, a, g);
   else if (u4_plain && !relu_step && all_whole)
-    hipLaunchKernelGGL((conv_first_kernel<KHW, 3>), dim3(blocks), dim3(256), lds, s, a, g);
+    hipLaunchKernelGGL((conv_first_kernel<KHW, TH, 3>), dim3(blocks), dim3(256), lds, s, a, g);
   else if (u4_plain)
-    hipLaunchKernelGGL((conv_first_kernel<KHW, 2>), dim3(blocks), dim3(256), lds, s, a, g);
+    hipLaunchKernelGGL((conv_first_kernel<KHW, TH, 2>), dim3(blocks), dim3(256), lds, s, a, g);
   else
-    hipLaunchKernelGGL((conv_first_kernel<KHW, 0>), dim3(blocks), dim3(256), lds, s, a, g);
+    hipLaunchKernelGGL((conv_first_kernel<KHW, TH, 0>), dim3(blocks), dim3(256), lds, s, a, g);
   return (int)hipGetLastError();
+}
+
+template <int KHW>
+static int launch_conv_first_rows(const GemmArgs& a, const FirstGeom& g, int rows, unsigned blocks, hipStream_t s) {
+  if (rows == 4) return launch_conv_first_t<KHW, 4>(a, g, blocks, s);
+  if (rows == CF_T) return launch_conv_first_t<KHW, CF_T>(a, g, blocks, s);
+  return launch_conv_first_t<KHW, 8>(a, g, blocks, s);
+}
+
+// Rows of a launch's tiles; tall: how many there would be of sixteen rows.  Few tiles: the launch is as long as one work-group's tile,
+// and with four rows that is a quarter of the blocks on four times the compute units.  From three work-groups per unit on (7x7; of the
+// smaller filters, whose tiles are shorter anyway, from one and a half on) what low tiles stage twice costs as much.  Eight rows against
+// sixteen stage an eighth more, from memory where other launches came before, but share out twice as finely, which counts up to two rounds of tiles.
+// us at 16 / 8 / 4 rows, 224 x 224, the same launch repeated: 7x7 to 64 channels with a bias, 1 image 5.9 / 4.3 / 4.4, 3 images 6.2 / 5.2 / 4.7,
+// 5 images 6.5 / 5.0 / 5.4, 16 images 9.6 / 8.1 / 8.5, 64 images 23.3 / 21.4 / 23.6; without one 5.3 / 4.4 / 4.0, 5.1 / 4.8 / 4.5, 5.5 / 4.8 / 5.0,
+// 8.3 / 7.7 / 8.1, 21.4 / 20.8 / 23.1; 3x3 to 32 with a bias 5.2 / 4.1 / 4.0, 5.0 / 4.4 / 4.6, 5.1 / 4.6 / 4.9, 6.9 / 6.3 / 7.1, 14.3 / 14.3 / 17.9;
+// 5x5, 32 images, 9.2 / 10.1 / 11.4.  Between the launches of a stack: 1 image 6.4 -> 4.5 with four rows; 64 images 22.3 / 23.4.
+static int first_rows(int KH, int tall) {
+  if (tall <= (KH == 7 ? 192 : 100)) return 4;
+  return tall <= 1200 ? 8 : CF_T;
 }
 
 // Launches the first-layer kernel when the layer fits it; *applied says whether it did.
 int try_launch_conv_first(const GemmArgs& a, void* stream, bool* applied) {
   *applied = conv_first_applies(a);
   if (!*applied) return 0;
-  last_dispatch() = DispatchRecord{DK_FIRST_LAYER};
   FirstGeom g;
   g.tiles_w = (a.OW + CF_T - 1) / CF_T;
-  g.tiles_h = (a.OH + CF_T - 1) / CF_T;
+  const int tall = a.d.B * g.tiles_w * ((a.OH + CF_T - 1) / CF_T);
+  const int forced = forced_split()[0] == 0 ? forced_split()[1] : 0;  // (the test hook: 4, 8 or 16 rows)
+  const int rows = forced == 4 || forced == 8 || forced == CF_T ? forced : first_rows(a.d.KH, tall);
+  last_dispatch() = DispatchRecord{DK_FIRST_LAYER, rows};
+  g.tiles_h = (a.OH + rows - 1) / rows;
   g.total_tiles = a.d.B * g.tiles_w * g.tiles_h;
   // Three work-groups share a compute unit (register budget): exactly that many work-groups when
   // there are enough tiles, the tiles spread evenly over them, so that every compute unit carries
@@ -480,14 +511,14 @@ int try_launch_conv_first(const GemmArgs& a, void* stream, bool* applied) {
   int n_wg = g.total_tiles < 768 ? g.total_tiles : 768;
   g.tiles_base = g.total_tiles / n_wg;
   g.tiles_rem = g.total_tiles % n_wg;
-  g.magic_tw = cf_div_magic(g.tiles_w);
-  g.magic_thw = cf_div_magic((int64_t)g.tiles_w * g.tiles_h);
+  g.by_tw = cf_div_of(g.tiles_w);
+  g.by_thw = cf_div_of((int64_t)g.tiles_w * g.tiles_h);
   const unsigned blocks = (unsigned)n_wg;
   hipStream_t s = (hipStream_t)stream;
   switch (a.d.KH) {
-    case 3: return launch_conv_first_t<3>(a, g, blocks, s);
-    case 5: return launch_conv_first_t<5>(a, g, blocks, s);
-    default: return launch_conv_first_t<7>(a, g, blocks, s);
+    case 3: return launch_conv_first_rows<3>(a, g, rows, blocks, s);
+    case 5: return launch_conv_first_rows<5>(a, g, rows, blocks, s);
+    default: return launch_conv_first_rows<7>(a, g, rows, blocks, s);
   }
 }
 

@@ -19,7 +19,8 @@ typedef int v16i __attribute__((ext_vector_type(16)));
 // has pushed the code out.  Fetched as it is run it comes line by line, in the way of every wave of the XCD at once; so the
 // first work-groups of each XCD read it as data when they start, all lines at once, and the fetches that follow find it in the L2.
 // For the first layer's and the FP6 patch kernels, between whose launches of a large batch 20 MB and more go through each L2: the stack of a
-// ResNet-18 at batch 64 212.8 -> 210.3 us (in another process 214.7 -> 208.8).  The tile, split, half and skinny kernels did
+// ResNet-18 at batch 64 212.8 -> 210.3 us (in other processes 217.5 -> 215.5, 214.7 -> 208.8); each kernel's first launch in it 13.7 -> 13.0,
+// 12.4 -> 11.6, 12.2 -> 11.6, those that follow their own kind the same.  The tile, split, half and skinny kernels did
 // not gain (six GEMMs of an encoder layer at 4096 tokens 54.5 / 54.9, the stack on one image 74.3 / 75.2), and have no such read.
 struct CodeRange {
   const void* at;

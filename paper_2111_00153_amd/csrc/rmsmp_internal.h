@@ -205,7 +205,7 @@ int launch_ste_backward(const SteArgs& a, void* stream);
 // Test hooks.  forced_split(): a wave split {pixel blocks per wave, K split, pixel blocks side by
 // side, tile pairs} the LDS-resident kernel should use where it fits the layer (all zero:
 // automatic); like last_dispatch() it belongs to the calling thread.  Without a wave split (first entry 0) the
-// second entry is a work-group shape of the FP6 or the skinny kernel, the third 1 for the int8 kernels
+// second entry is a work-group shape of the FP6 or the skinny kernel or the rows of the first-layer kernel's tiles, the third 1 for the int8 kernels
 // only and 2 for the general kernel only.
 // last_dispatch(): which kernel the calling thread's last call of the library went to; whoever launches writes all of it.
 enum DispatchKernel {
@@ -216,7 +216,7 @@ struct DispatchRecord {
   int kernel = DK_NONE;
   // LDS-resident: the wave split.  FP6 tile: column blocks per wave, waves along the rows, waves along the columns,
   // kernel variant (1 convolution + 2 ragged columns).  Split kernels: waves, 0, 0, variant.  FP6 patch: column blocks per wave, K split,
-  // waves along the columns, pairs of tiles; LDS-resident pair: the same where that kernel runs it, else zeros.
+  // waves along the columns, pairs of tiles; LDS-resident pair: the same where that kernel runs it, else zeros.  First layer: rows of a tile.
   int xb = 0, ks = 0, nwt = 0, ms = 0;
 };
 int* forced_split();
