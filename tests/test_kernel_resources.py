@@ -74,3 +74,11 @@ def test_lds_resident_kernels_without_a_bias_have_the_registers_their_estimates_
     assert {a: use for a, use in three.items() if use[0] > 168} == {} and len(three) == 7
     whole = {a: use for a, use in wide.items() if a[3] == 1}
     assert {a: use for a, use in whole.items() if use[1] != 0} == {} and len(whole) > 20
+
+
+def test_patch_kernels_keep_their_sums_in_registers(kernels):
+    """Template arguments: blocks per wave, K split, pairs of tiles, waves along the columns, ragged.  Two waves share a SIMD (at most 256
+    registers), and none spills: the estimates of ten shapes, and of three with two layers in a launch, assume both."""
+    patch, pair = _named(kernels, "fp6_patch_kernel"), _named(kernels, "fp6_patch_pair_kernel")
+    assert {a: use for a, use in {**patch, **pair}.items() if use[0] > 256 or use[1] != 0} == {}
+    assert len(patch) == 10 * 2 and len(pair) == 3
