@@ -235,6 +235,76 @@ def test_conv_patch_kernel(rm, oracle, shape, geom, M, ratio):
         p.free()
 
 
+# rows whose sums are just below 2^24, as test_mixed_sums_just_below_what_fp32_holds has for the kernels that take GEMMs: 5 x 6 filters, whose K is deep
+# enough (for PoT rows as many channels as the shape's patch has room for: 256 columns reach 0.93 of the bound, 512 reach 0.49)
+@pytest.mark.parametrize("shape", sorted(PATCHES))
+@pytest.mark.parametrize("rows", ["pot4", "fixed8", "both"])
+def test_sums_just_below_what_fp32_holds_patch_kernel(rm, oracle, rows, shape):
+    """Tiles in one part, in two, one of each in a wave, one left over: the largest and the smallest level in one instruction,
+    small products on top of a large sum, a large sum and back to nothing, odd sums, both signs; the partial sums of waves that share K."""
+    tn, _, wn, _ = PATCHES[shape]
+    cols = 32 * tn * wn
+    C = 288 if rows != "pot4" else 592 if cols <= 128 else 544 if cols == 256 else 288
+    B, H, Wd, KH, KW, M = 2, 7, 11, 5, 6, 66 if rows != "both" else 64
+    K = C * KH * KW
+    rng = np.random.default_rng(240 + shape)
+    limit = ((1 << 24) - 1) // 15
+    scheme = np.full(M, 1 if rows == "pot4" else 2, np.uint8)
+    if rows == "both":  # (a tile of each)
+        scheme[:32] = 1
+    Q = np.zeros((M, K), np.int64)
+    for r in range(M):
+        pot = scheme[r] == 1
+        levels = np.array([0] + [s * 2 ** e for s in (-1, 1) for e in range(7)]) if pot else np.arange(-127, 128)
+        q = np.full(K, 64 if pot else 127)
+        kind = r % 32
+        if kind == 1:
+            q[::16] = 1
+        elif kind == 2:
+            q[::16] = -1
+        elif kind == 3:
+            q[K // 2:] *= -1
+        elif kind == 4:
+            q = -q
+            q[1::32] = 1
+        elif kind == 5:
+            q[K - K // 8:] = 1
+        elif kind == 6:
+            q[: K // 8] = 1
+        elif kind > 6:
+            q = rng.choice(levels, K)
+        h = (q + 8) >> 4
+        cost = np.abs(q) if pot else 16 * np.abs(h) + np.abs(q - 16 * h)  # what the operands hold of a level
+        q[np.cumsum(cost) > limit] = 0
+        Q[r] = q
+    W = (Q / np.where(scheme == 1, 64.0, 127.0)[:, None]).astype(np.float32)
+    alpha = np.ones(M, np.float32)
+    ref = oracle.quantize_rows(W, scheme, alpha=alpha)
+    assert np.array_equal(ref["wint"], Q)
+    x = si.act_codes_u4(rng, (B, H, Wd, C))
+    x[0] = 15
+    x[0, :, -1, 1::2] = 14
+    od = oracle.conv_desc(B, C, H, Wd, KH, KW, 1, 2)
+    OH, OW = oracle.conv_out_hw(od)
+    acc = oracle.conv_acc(ref["wint"].reshape(M, C, KH, KW), x.astype(np.int32), od, zpad=0)
+    reach = 0.98 if rows != "pot4" or cols <= 128 else 0.92 if cols == 256 else 0.49
+    assert reach * (1 << 24) < int(np.abs(acc).max()) < 1 << 24 and (acc % 2).any()
+    p = rm.rmsmp_pack_weights(W, scheme, alpha=alpha, taps=KH * KW)
+    d = rm.ConvDesc(B, C, H, Wd, KH, KW, 1, 2)
+    need = rm.rmsmp_conv2d_workspace_size(p, d, 4)
+    ws = torch.empty((need,), dtype=torch.uint8, device=DEV) if need else None
+    Y = torch.full((M, B * OH * OW), -777, dtype=torch.int32, device=DEV)
+    rm.rmsmp_debug_set_wave_split(0, shape, 0, 0)
+    try:
+        rm.rmsmp_conv2d(p, _to_dev(rm.pack_u4(x)), d, rm.make_epilogue(0.05, 0, 4, None, False, rm.OUT_INT32), Y, ws)
+        assert rm.rmsmp_debug_last_dispatch() == ("fp6_patch", PATCHES[shape])
+    finally:
+        rm.rmsmp_debug_set_wave_split(0, 0, 0, 0)
+    torch.cuda.synchronize()
+    assert np.array_equal(Y.cpu().numpy(), acc)
+    p.free()
+
+
 @pytest.mark.parametrize("shape", HALVES)
 @pytest.mark.parametrize("scheme_code", [1, 2])
 def test_mixed_sums_just_below_what_fp32_holds_half_tiles(rm, oracle, scheme_code, shape):
