@@ -38,20 +38,21 @@ template <int ID>
 __device__ __forceinline__ void code_end() {
   asm volatile(".Lrmsmp_code_end_%c0:" ::"i"(ID));
 }
-// Wave `wave` of the launch's waves on its XCD reads its 8 KB of the code, a dword of each line of 128 bytes.  The result goes to
-// code_touched, behind the wait for a later read.
+// Wave `wave` of the launch's waves on its XCD, one of the first READERS, reads its 8 KB of the code, a dword of each line of 128 bytes (what
+// lies beyond the readers' share is fetched as it is run).  The result goes to code_touched, behind the wait for a later read.
+template <int READERS>
 __device__ __forceinline__ unsigned touch_code(const CodeRange& c, int wave) {
   const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(c.at), 0, (int)c.bytes, 0x00020000);
-  const unsigned off = wave < 8 ? (unsigned)wave * 8192u + (threadIdx.x & 63) * 128u : 0x80000000u;
+  const unsigned off = wave < READERS ? (unsigned)wave * 8192u + (threadIdx.x & 63) * 128u : 0x80000000u;
   const unsigned v = __builtin_amdgcn_raw_buffer_load_b32(r, (int)off, 0, 0);
   __builtin_amdgcn_sched_barrier(0);
   return v;
 }
 __device__ __forceinline__ void code_touched(unsigned v) { asm volatile("" ::"v"(v)); }
-// (work-groups go to the eight XCDs in turn)
-template <int ID, int WAVES>
+// (work-groups go to the eight XCDs in turn; eight waves read 64 KB, which every kernel of one layer fits)
+template <int ID, int WAVES, int READERS = 8>
 __device__ __forceinline__ unsigned touch_kernel() {
-  return touch_code(code_here<ID>(), (int)(blockIdx.x >> 3) * WAVES + __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6));
+  return touch_code<READERS>(code_here<ID>(), (int)(blockIdx.x >> 3) * WAVES + __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6));
 }
 
 // ---------------------------------------------------------------- operand decode

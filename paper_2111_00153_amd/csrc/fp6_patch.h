@@ -270,8 +270,8 @@ __device__ __forceinline__ float patch_wave(const Fp6Args& a, const Fp6Patch& g,
   return bias;
 }
 
-// ID: see code_here.
-template <int TN, int KS, int WM, int WN, bool RAGGED, int ID>
+// ID: see code_here.  READERS: the waves that read the code when the launch starts (touch_code), none where another body of the kernel does.
+template <int TN, int KS, int WM, int WN, bool RAGGED, int ID, int READERS = 8>
 __device__ __forceinline__ void patch_body(const PatchFirst& f, const Fp6Args& a, const Fp6Patch& g, const int block) {
   using S = PatchShape<TN, KS, WM, WN>;
   extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
@@ -301,7 +301,8 @@ __device__ __forceinline__ void patch_body(const PatchFirst& f, const Fp6Args& a
 
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const unsigned touched = touch_kernel<ID, S::NW>();
+  unsigned touched = 0;
+  if constexpr (READERS > 0) touched = touch_kernel<ID, S::NW, READERS>();
   const int kq = wave % KS, wn = wave / KS % WN, wm = wave / (KS * WN);
   const int q = by * WM + wm;  // (past the last pair: helps to stage the patch)
   const Fp6Pair pair = fp6_pair_joined(a, q < a.pairs ? q : a.pairs - 1);
@@ -322,7 +323,7 @@ __device__ __forceinline__ void patch_body(const PatchFirst& f, const Fp6Args& a
     RMSMP_PATCH_WAVE(2, false, false);
   }
 #undef RMSMP_PATCH_WAVE
-  code_touched(touched);
+  if constexpr (READERS > 0) code_touched(touched);
   float* const meta = (float*)smem + wave * (FM_FIELDS * 64);
   meta[FM_BIAS * 64 + lane] = bias;
 

@@ -7,17 +7,19 @@
 
 namespace rmsmp {
 
+// The first layer's work-groups, which start first, read the code of both: up to 82 KB.
+constexpr int PAIR_READERS = 12;
+
 // Two layers on one input, the first blocks_a work-groups the first's (rmsmp_conv2d_pair).
 template <int TN, int KS, int WM, int WN>
 __global__ __launch_bounds__(LANES * KS * WM * WN, 2) void fp6_patch_pair_kernel(FP6_PATCH_FIRST_PARAMS, Fp6Args a, Fp6Patch g, PatchFirst first_b, Fp6Args b, Fp6Patch g_b, int blocks_a) {
   constexpr int ID = patch_id<TN, KS, WM, WN>();
   const int block = (int)blockIdx.x;
   if (block < blocks_a)
-    patch_body<TN, KS, WM, WN, false, 2 * ID>(FP6_PATCH_FIRST_UNPACK(), a, g, block);
+    patch_body<TN, KS, WM, WN, false, ID, PAIR_READERS>(FP6_PATCH_FIRST_UNPACK(), a, g, block);
   else
-    patch_body<TN, KS, WM, WN, false, 2 * ID + 1>(first_b, b, g_b, block - blocks_a);
-  code_end<2 * ID>();
-  code_end<2 * ID + 1>();
+    patch_body<TN, KS, WM, WN, false, ID, 0>(first_b, b, g_b, block - blocks_a);
+  code_end<ID>();
 }
 
 template <int TN, int KS, int WM, int WN>

@@ -29,6 +29,21 @@ def _code_objects(data):
 
 
 @pytest.fixture(scope="module")
+def code_bytes(tmp_path_factory):
+    """{(name, template arguments): bytes of code}"""
+    found = {}
+    path = tmp_path_factory.mktemp("code") / "object"
+    with open(LIB, "rb") as f:
+        data = f.read()
+    for obj in _code_objects(data):
+        path.write_bytes(obj)
+        symbols = subprocess.run([READELF, "--symbols", "--wide", str(path)], capture_output=True, text=True, check=True).stdout
+        for size, name, arguments in re.findall(r"\s(\d+) FUNC .* _ZN5rmsmp\d+([a-z0-9_]+_kernel)I((?:L[ib]\d+E)+)E", symbols):
+            found[name, tuple(int(v) for v in re.findall(r"L[ib](\d+)E", arguments))] = int(size)
+    return found
+
+
+@pytest.fixture(scope="module")
 def kernels(tmp_path_factory):
     """{(name, template arguments): (registers, bytes of scratch)}"""
     found = {}
@@ -82,3 +97,10 @@ def test_patch_kernels_keep_their_sums_in_registers(kernels):
     patch, pair = _named(kernels, "fp6_patch_kernel"), _named(kernels, "fp6_patch_pair_kernel")
     assert {a: use for a, use in {**patch, **pair}.items() if use[0] > 256 or use[1] != 0} == {}
     assert len(patch) == 10 * 2 and len(pair) == 3
+
+
+def test_kernels_that_read_their_code_have_readers_for_all_of_it(code_bytes):
+    """The first waves of a launch on each XCD read 8 KB each: eight of them, twelve where a launch has two layers."""
+    for name, readers, count in (("fp6_patch_kernel", 8, 10 * 2), ("conv_first_kernel", 8, 3 * 3 * 4), ("fp6_patch_pair_kernel", 12, 3)):
+        sizes = _named(code_bytes, name)
+        assert len(sizes) == count and max(sizes.values()) <= readers * 8192, (name, sizes)
