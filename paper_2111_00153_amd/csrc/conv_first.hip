@@ -64,7 +64,7 @@ __global__ __launch_bounds__(256, 3) void conv_first_kernel(GemmArgs a, FirstGeo
   constexpr int NUNIT = PH * CF_UNITS;
   constexpr int UPT = (NUNIT + 255) / 256;   // units per thread
   constexpr int ID = (KHW * 32 + TH) * 4 + MODE_;
-  const unsigned touched = touch_kernel<ID, 4>();
+  unsigned touched = touch_kernel<ID, 4>();
   const EpArgs ea = pin_epilogue_args(a);
   const int tid = threadIdx.x;
   const int lane = tid & 63;
@@ -235,6 +235,7 @@ __global__ __launch_bounds__(256, 3) void conv_first_kernel(GemmArgs a, FirstGeo
     __syncthreads();  // metadata stored / previous pass done with both buffers
     store_units(pos0, raw0, buf0);
     code_touched(touched);
+    touched = 0;  // (no register of the tile loop is held for it)
     __syncthreads();
 
     const int n_rows = mine_live ? lane_rows(tr.nvalid, lane) : 0;

@@ -104,3 +104,10 @@ def test_kernels_that_read_their_code_have_readers_for_all_of_it(code_bytes):
     for name, readers, count in (("fp6_patch_kernel", 8, 10 * 2), ("conv_first_kernel", 8, 3 * 3 * 4), ("fp6_patch_pair_kernel", 12, 3)):
         sizes = _named(code_bytes, name)
         assert len(sizes) == count and max(sizes.values()) <= readers * 8192, (name, sizes)
+
+
+def test_first_layer_kernels_spill_nothing_in_their_plain_loops(kernels):
+    """Template arguments: filter side, rows of a tile, loop.  Whole 4-bit rows without a bias (1), with one (3), any 4-bit rows (2); the 7x7
+    filter's 16 rows with a bias hold three blocks of fragments and spill five registers."""
+    first = {a: use for a, use in _named(kernels, "conv_first_kernel").items() if a[2] != 0}
+    assert {a: use[1] for a, use in first.items() if use[1] != 0} in ({}, {(7, 16, 3): 20}) and len(first) == 3 * 3 * 3
