@@ -144,6 +144,16 @@ def test_pair_on_the_patch_kernel(rm, oracle, C, MA, MB, H, W, shape):
     Bl.p.free()
 
 
+@pytest.mark.parametrize("shape", [1, 6, 7, 10, 15, 20, 24])
+def test_pair_that_is_asked_for_in_a_shape_of_other_calls(rm, oracle, shape):
+    """Numbers that no two-layer launch has: too many columns for half tiles, so the int8 launch of both."""
+    X, A, Bl = _pair(rm, oracle, 79, 12, 64, 56, 56, 128, 128, 2, 3)
+    _run_all_kinds(rm, X, A, Bl, 3, "lds_resident_pair", (0, shape, 0, 0))
+    assert rm.rmsmp_debug_last_dispatch()[1] == (0, 0, 0, 0)
+    A.p.free()
+    Bl.p.free()
+
+
 def test_pair_with_odd_sides_is_one_launch(rm, oracle):
     """Small enough for half tiles; the int8 two-layer launch does not take such images."""
     X, A, Bl = _pair(rm, oracle, 78, 2, 128, 15, 13, 96, 96, 2, 5)
