@@ -207,19 +207,50 @@ static bool wide_kernel_applies(const GemmArgs& a0, WidePlan* plan) {
   return true;
 }
 
-// What a plan takes in us, for the choice against the FP6 kernels (fp6_gemm.hip says what it was fitted to): unlike the
-// cycles above, which only rank the splits of one call, with the output kind, the class mix and the XCDs.
+// Table-decoded tiles in the heaviest pair: tiles are sorted by class, pair y is tile y and tile n - 1 - y, so two of
+// them meet only in the innermost pair.  (As a share of all tiles the 512-channel 3x3 layers at 7x7 with 35 to 40 % PoT
+// rows came out 6 % too slow, and went to the 6-bit kernels: 8.2 us here, 8.9 there.)
+static int wide_heaviest_decode(const DevicePacked& w) {
+  const int n = w.n_tiles, first = w.class_tiles[TILE_NIB_SHIFT], count = w.class_tiles[TILE_NIB_LUT], inner = (n - 2) / 2;
+  return n >= 2 && first <= inner && n - 1 - inner < first + count ? 2 : count > 0 ? 1 : 0;
+}
+
+// What a 3x3 layer's plan takes in us, for the choice against the FP6 kernels: unlike the cycles above, which only rank the splits of
+// one call, with the output kind, the class mix, the XCDs, and the heaviest work-group beside the mean one.  Only table-decoded tiles cost
+// more than others here; PoT rows stored as int8 have none, while on the 6-bit instructions they double the products of their tiles.
+// Fitted to 1 500 layers of 64 to 512 channels (16 to 1024 rows, images of 7 to 80 pixels, strides 1 and 2, 1 to 64 of them, nine class
+// ratios in both storages, 4.5 to 100 us): 5 % off.  (The estimate that 3x3 layers shared with 1x1 layers and GEMMs was 11 % off, 3 to 8 %
+// too slow with PoT rows as int8, and too fast where the last row of work-groups is not whole: 512 to 848 channels, 2 x 65 x 65, 31 us where it took 57.)
+static float wide_3x3_us(const WidePlan& p) {
+  const GemmArgs& a = p.a;
+  const bool x4 = p.xb == 4;
+  const int pairs = (a.w.n_tiles + 1) / 2;
+  const float heaviest = (float)wide_heaviest_decode(a.w), mean = (float)a.w.class_tiles[TILE_NIB_LUT] / (float)pairs;
+  const float decode = x4 ? 0.144f : 0.481f;
+  const float kloop = 9.0f * p.cpt / p.ks * 2.0f * p.xb * (x4 ? 0.0169f : 0.0179f) * (1.0f - (p.nwt > 1 ? 0.0521f : 0.0f) + (p.ms == 4 ? 0.1f : 0.0f) - (p.ks == 4 ? 0.0765f : 0.0f)) *
+                      (a.w.n_tiles == 1 ? 0.88f : 1.0f);
+  const bool out32 = a.ep.out_kind <= 1, unaligned = !out32 && a.M % 16 != 0;
+  const float block = 0.32f + (out32 ? 0.77f : 0.0f) + (a.ep.out_kind == 3 ? 1.29f : 0.0f) + (unaligned ? 0.628f : 0.0f) + (a.ep.bias ? 0.0643f : 0.0f);
+  const float rest = 1.34e-5f * p.g.patch_rows * p.g.row_stride + (p.ks > 1 ? 1.88e-5f * pw_xch_bytes(p.xb, p.ks, p.ks * p.nwt * p.ms) : 0.0f) + 2.0f * p.xb / p.ks * block;
+  // (a last row of work-groups whose waves are not all there costs a third of what they would)
+  const float group = (rest + kloop * (1.0f + decode * mean)) * (1.0f - 0.361f * (1.0f - (float)pairs / (float)(p.g.gy * p.ms)));
+  const int by_lds = (int)((160 * 1024) / p.lds), share = std::min(by_lds, x4 ? 2 : 3);
+  const float per_unit = (float)((p.g.gx + 7) / 8 * p.g.gy) / 32.0f;  // (the column blocks are dealt out to the eight XCDs)
+  const float n = std::max(1.0f, per_unit + (share == 1 ? 0.79f : 0.673f) * (whole_up(per_unit) - per_unit));
+  const float further = std::max(0.0f, n - (float)share) * (share == 1 ? 1.33f : x4 ? 0.876f : 1.1f);
+  const float megabytes = (float)((double)a.M * a.N * 4e-6);
+  return 3.01f + rest + kloop * (1.0f + decode * heaviest) + ((std::min(n, (float)share) - 1.0f) * (x4 ? 0.794f : 0.722f) + further) * group +
+         (out32 ? 0.0778f * megabytes : unaligned ? 0.074f * megabytes : 0.0f);
+}
+
+// The same for 1x1 layers and GEMMs (fp6_gemm.hip says what it was fitted to; those with K = 9 C run as 3x3 layers on images of 3x3 pixels).
 static float wide_us(const WidePlan& p) {
   const GemmArgs& a = p.a;
   const int taps = a.d.KH * a.d.KW;
   const bool x4 = p.xb == 4, nine = taps == 9;
   const float mfmas = (float)taps * p.cpt * p.g.nchunk / p.ks * 2 * p.xb;
-  // table-decoded tiles in the heaviest pair: tiles are sorted by class, pair y is tile y and tile n - 1 - y, so two of
-  // them meet only in the innermost pair.  (As a share of all tiles the 512-channel 3x3 layers at 7x7 with 35 to 40 % PoT
-  // rows came out 6 % too slow, and went to the 6-bit kernels: 8.2 us here, 8.9 there.)
-  const int n_tiles = a.w.n_tiles, lut0 = a.w.class_tiles[TILE_NIB_SHIFT], lut_tiles = a.w.class_tiles[TILE_NIB_LUT], inner = (n_tiles - 2) / 2;
-  const bool both = n_tiles >= 2 && lut0 <= inner && n_tiles - 1 - inner < lut0 + lut_tiles;
-  const float decode = both ? 0.928f : lut_tiles > 0 ? 0.47f : 0.0f;
+  const int heaviest = wide_heaviest_decode(a.w);
+  const float decode = heaviest == 2 ? 0.928f : heaviest == 1 ? 0.47f : 0.0f;
   const float kloop = mfmas * (x4 ? (nine ? 0.0179f : 0.021f) : 0.018f * (1.0f + decode));
   const float stage = 1.34e-5f * p.g.patch_rows * p.g.row_stride;
   const bool out32 = a.ep.out_kind <= 1, unaligned = !out32 && a.M % 16 != 0, bias = a.ep.out_kind == 2 && a.ep.bias;
@@ -257,11 +288,18 @@ static int launch_wide(const WidePlan& p, hipStream_t s) {
   return (int)hipErrorInvalidValue;
 }
 
+static float wide_plan_us(const WidePlan& p, bool conv) { return conv && p.a.d.KH * p.a.d.KW == 9 ? wide_3x3_us(p) : wide_us(p); }
+
+float wide_layer_us(const GemmArgs& a) {
+  WidePlan plan;
+  return wide_kernel_applies(a, &plan) ? wide_plan_us(plan, a.conv) : std::numeric_limits<float>::infinity();
+}
+
 // Launches the wide kernel when the layer fits it and it is estimated to take less than limit_us; *applied says
 // whether it did.
 int try_launch_wide(const GemmArgs& a, void* stream, float limit_us, bool* applied) {
   WidePlan plan;
-  *applied = wide_kernel_applies(a, &plan) && (std::isinf(limit_us) || wide_us(plan) < limit_us);
+  *applied = wide_kernel_applies(a, &plan) && (std::isinf(limit_us) || wide_plan_us(plan, a.conv) < limit_us);
   const int* forced = forced_split();
   if (*applied && forced[0] > 0) {
     WidePlan p2;

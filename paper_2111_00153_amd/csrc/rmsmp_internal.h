@@ -229,6 +229,8 @@ int launch_gemm(const GemmCall& a, void* stream);
 // LDS-resident implicit-im2col kernel (patch_wide.hip): launches when the layer fits it and says
 // so in *applied.  limit_us: only if it is estimated to take less.
 int try_launch_wide(const GemmArgs& a, void* stream, float limit_us, bool* applied);
+// What that is estimated to take, in us (infinity: the kernel does not take the layer).
+float wide_layer_us(const GemmArgs& a);
 // The same kernel for two layers that read one input (a 3x3 and a 1x1 layer), as one launch.
 int try_launch_wide_pair(const GemmCall& a, const GemmCall& b, void* stream, bool* applied);
 // FP6 kernels (fp6_gemm.hip); same convention.
