@@ -156,17 +156,33 @@ bool fp6_patch_choose(const Fp6Args& a, bool ragged, int KH, int B, int* shape, 
   return any;
 }
 
-// Both layers in one shape: their work-groups one after the other, the first layer's at the front.  (246 stage heads: 0.98 of the time
-// they take on average, 4 % off.)
+// Both layers in one shape: the larger layer's work-groups, and where those leave room on the units, or else behind them, the other's.  us, by
+// shape: what the launch takes besides; shares of a work-group's time, as in PatchTime: of the heaviest one, of a second one on its unit, of one more beyond
+// what the units hold, two each and one each; of the other layer's, whose few products leave the rest of it standing; of the places beside the
+// larger layer's work-groups, those that take one of the other's without delay; per megabyte of 32-bit output.
+// Fitted to 1 800 stage heads (64 to 256 channels, 64 to 1024 rows, 1 to 64 images of 8 to 62 pixels, nine class ratios in both storages): 5 to 7 % off;
+// the shape picked takes 1.006 times as long as the best of the three, 95 of 100 within 1.04 (1.017 and 1.11 with every work-group as the mean one).
+struct PatchPairTime {
+  float launch, alone, share, rate2, rate1, other, free, megabyte;
+};
+static const PatchPairTime kPatchPairs[PATCH_PAIR_SHAPES] = {
+    {4.05f, 0.938f, 0.838f, 0.752f, 1.05f, 2.63f, 0.63f, 0.0932f}, {3.8f, 0.897f, 0.594f, 0.607f, 0.969f, 2.67f, 0.497f, 0.0883f}, {2.13f, 0.939f, 0.0f, 0.0f, 0.797f, 2.2f, 0.0f, 0.11f}};
 bool fp6_patch_choose_pair(const Fp6Args& a, int KHa, const Fp6Args& b, int KHb, int B, int* shape, float* us) {
   bool any = false;
+  const float megabytes = (a.out_kind <= 1 ? (float)((double)a.M * a.N * 4e-6) : 0.0f) + (b.out_kind <= 1 ? (float)((double)b.M * b.N * 4e-6) : 0.0f);
   for (int i = 0; i < PATCH_PAIR_SHAPES; ++i) {
     const PatchShapeInfo& s = kPatchShapes[i];
+    const PatchPairTime& t = kPatchPairs[i];
     PatchPlan p, q;
     if (!patch_plan(a, KHa, B, i, &p) || !patch_plan(b, KHb, B, i, &q)) continue;
     const PatchGroup ga = patch_group_us(a, p, s, false), gb = patch_group_us(b, q, s, false);
-    const float na = patch_per_unit(p.f), nb = patch_per_unit(q.f);
-    const float time = patch_launch_us(PatchGroup{std::max(ga.alone, gb.alone), (na * ga.mean + nb * gb.mean) / (na + nb)}, na + nb, std::max(p.lds, q.lds), s);
+    const float na = patch_per_unit(p.f), nb = patch_per_unit(q.f), cap = patch_per_cu(s, std::max(p.lds, q.lds));
+    const bool first = ga.mean >= gb.mean;
+    const float large = first ? na : nb, other = first ? nb : na, mean = first ? ga.mean : gb.mean, ratio = (first ? gb.mean : ga.mean) / mean;
+    const float whole = std::max(1.0f, whole_up(large));
+    const float n = std::max(whole, large + t.other * std::max(0.0f, other - t.free * std::max(0.0f, cap - whole)) * ratio);
+    const float time = t.launch + t.alone * std::max(ga.alone, gb.alone) +
+                       ((std::min(n, cap) - 1.0f) * t.share + std::max(0.0f, n - cap) * (cap > 1.0f ? t.rate2 : t.rate1)) * mean + t.megabyte * megabytes;
     if (time < *us) *us = time, *shape = i, any = true;
   }
   return any;

@@ -310,18 +310,40 @@ int try_launch_wide(const GemmArgs& a, void* stream, float limit_us, bool* appli
   return launch_wide(plan, (hipStream_t)stream);
 }
 
-// What the two-layer launch takes, in us: 101 stage heads of 64, 128 and 256 channels (7 to 17 us) within about 15 %; with biases
-// the general epilogue is 1.6 us longer.  (per_unit: of the 3x3 layer's work-groups.)
-static float wide_pair_us(int cpt, const WidePlan& a, bool bias) {
-  const float per_unit = (float)a.blocks / 256.0f;
-  const float us = cpt == 2 ? 7.9f + 5.3f * std::max(0.0f, per_unit - 0.65f) : cpt == 4 ? 7.3f + 2.5f * per_unit : 6.2f + 8.0f * per_unit;
-  return us + (bias ? 1.6f : 0.0f);
+// What the two-layer launch takes, in us, as wide_3x3_us: the larger layer's work-groups, and where those leave room on the units, or
+// else behind them, the other's.  Fitted to 500 stage heads (64, 128 and 256 channels, 64 to 1024 rows, 1 to 64 images of 8 to 62 pixels, nine class
+// ratios in both storages): 7 % off, as on 760 others.  (Without the class mix, the storage and the rows it was 26 % off, mostly too fast: 256 to 672
+// channels, 48 x 42 x 42, 69 us where it took 115 and two launches take 40.)
+struct WidePairGroup {
+  float alone, mean, per_unit;
+};
+static WidePairGroup wide_pair_group(const WidePlan& p) {
+  const GemmArgs& a = p.a;
+  const int pairs = (a.w.n_tiles + 1) / 2;
+  const float kloop = (float)(a.d.KH * a.d.KW * p.cpt) / p.ks * 2.0f * p.xb * 0.012f, decode = p.xb == 4 ? 0.196f : 0.558f;
+  const bool out32 = a.ep.out_kind <= 1, unaligned = !out32 && a.M % 16 != 0;
+  const float block = 0.604f + (out32 ? 0.83f : 0.0f) + (unaligned ? 0.516f : 0.0f) + (a.ep.bias ? 0.0963f : 0.0f);
+  const float rest = 1.22e-5f * p.g.patch_rows * p.g.row_stride + (p.ks > 1 ? 7.34e-6f * pw_xch_bytes(p.xb, p.ks, p.ks * p.nwt * p.ms) : 0.0f) + 2.0f * p.xb / p.ks * block + (a.ep.bias ? 0.306f : 0.0f);
+  const float mean = (rest + kloop * (1.0f + decode * (float)a.w.class_tiles[TILE_NIB_LUT] / (float)pairs)) * (1.0f - 0.269f * (1.0f - (float)pairs / (float)(p.g.gy * p.ms)));
+  return WidePairGroup{rest + kloop * (1.0f + decode * (float)wide_heaviest_decode(a.w)), mean, (float)((p.g.gx + 7) / 8 * p.g.gy) / 32.0f};
+}
+static float wide_pair_us(const WidePlan& pa, const WidePlan& pb) {
+  const WidePairGroup a = wide_pair_group(pa), b = wide_pair_group(pb);
+  const WidePairGroup &large = a.mean >= b.mean ? a : b, &small = a.mean >= b.mean ? b : a;
+  const float share = 160 * 1024 / std::max(pa.lds, pb.lds) >= 2 ? 2.0f : 1.0f;
+  const float n = std::max(std::max(1.0f, whole_up(large.per_unit)), large.per_unit + (small.per_unit + 0.662f) * small.mean / large.mean);
+  float us = 3.41f + std::max(a.alone, b.alone) + ((std::min(n, share) - 1.0f) * 0.52f + std::max(0.0f, n - share) * (share == 1.0f ? 1.61f : 0.894f)) * large.mean;
+  for (const WidePlan* p : {&pa, &pb}) {
+    const float megabytes = (float)((double)p->a.M * p->a.N * 4e-6);
+    us += p->a.ep.out_kind <= 1 ? 0.0213f * megabytes : p->a.M % 16 != 0 ? 0.0545f * megabytes : 0.0f;
+  }
+  return us;
 }
 
 // Two layers on the same input as one launch (see conv_wide_pair_kernel): a 3x3 and a 1x1
 // layer with the same 64, 128 or 256 input channels, both with 4-bit activations, neither with
 // the GELU epilogue: the FP6 kernels where they are faster, which take images of odd sizes too, or this one where both layers fit the
-// split the pair kernel is built with.  *applied says whether
+// split the pair kernel is built with, or none where two launches are.  *applied says whether
 // the launch happened; if not, the caller launches the layers one after the other.
 int try_launch_wide_pair(const GemmCall& a0, const GemmCall& b0, void* stream, bool* applied) {
   *applied = false;
@@ -339,9 +361,10 @@ int try_launch_wide_pair(const GemmCall& a0, const GemmCall& b0, void* stream, b
     fits = (a.w.n_tiles + 1) / 2 >= sp.ma && (b.w.n_tiles + 1) / 2 >= sp.mb && wide_plan_mode(a, cca, sp.xa, sp.ka, sp.na, sp.ma, &pa) &&
            wide_plan_mode(b, ccb, sp.xb, sp.kb, sp.nb, sp.mb, &pb) && (uint64_t)pa.blocks + pb.blocks <= 0x7fffffffu;
   }
-  const float int8_us = fits ? wide_pair_us(cpt, pa, a0.ep.bias || b0.ep.bias) : std::numeric_limits<float>::infinity();
-  if (const int rc = try_launch_fp6_pair(a0, b0, int8_us, stream, applied); rc != 0 || *applied) return rc;
-  if (!fits) return 0;
+  const float int8_us = fits ? wide_pair_us(pa, pb) : std::numeric_limits<float>::infinity();
+  bool apart = false;
+  if (const int rc = try_launch_fp6_pair(a0, b0, int8_us, stream, applied, &apart); rc != 0 || *applied) return rc;
+  if (!fits || apart) return 0;
   *applied = true;
   last_dispatch() = DispatchRecord{DK_LDS_RESIDENT_PAIR};
 #define RMSMP_WIDE_CASE(CP) \

@@ -238,8 +238,9 @@ int try_launch_fp6(const GemmCall& a, void* stream, bool* applied);
 // Those or the LDS-resident kernel, whichever is estimated to be faster.
 int try_launch_tiled(const GemmCall& a, void* stream, bool* applied);
 // Two convolutions on one input as one launch of the FP6 split kernel or the patch kernel, where that is estimated to be faster
-// than the LDS-resident kernel, which takes int8_us (infinity: it does not take both), or than two launches.
-int try_launch_fp6_pair(const GemmCall& a, const GemmCall& b, float int8_us, void* stream, bool* applied);
+// than the LDS-resident kernel, which takes int8_us (infinity: it does not take both), and than two launches.  *apart: those are
+// the fastest.
+int try_launch_fp6_pair(const GemmCall& a, const GemmCall& b, float int8_us, void* stream, bool* applied, bool* apart);
 // Skinny kernel (skinny.hip).
 int try_launch_skinny(const GemmArgs& a, void* stream, bool* applied);
 // Split kernel on int8 instructions (i8_split.hip).
