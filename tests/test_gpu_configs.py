@@ -212,6 +212,43 @@ def test_config3_stage_heads_as_one_launch_batch64_sampled(rm, oracle, head):
     torch.cuda.empty_cache()
 
 
+@pytest.mark.parametrize("head,chosen", [("layer2.0", (2, 1, 2, 2)), ("layer3.0", (0, 0, 0, 0)), ("layer4.0", (2, 2, 1, 2))])
+def test_config3_stage_heads_on_every_two_layer_kernel_batch64_sampled(rm, oracle, head, chosen):
+    """The same heads on the int8 two-layer kernel (numbers of the record: zeros) and on each shape of the FP6 patch kernel's, whichever of them
+    is the one chosen, with the record that says which ran."""
+    names = [c[0] for c in si.RESNET18_CONVS]
+    ia, ib = names.index(head + ".conv1"), names.index(head + ".downsample")
+    A = _layer_reference(rm, oracle, ia, 64, 4000, structured=True)
+    Bl = _layer_reference(rm, oracle, ib, 64, 4000, structured=True, x=A["x"])
+    X = _dev(rm.pack_u4(A["x"]))
+    ran = {(0, 0, 0, 0): chosen, (0, 0, 1, 0): (0, 0, 0, 0), (0, 32, 0, 0): (2, 1, 2, 2), (0, 33, 0, 0): (2, 2, 1, 2), (0, 34, 0, 0): (2, 4, 1, 2)}
+    try:
+        for request, record in ran.items():
+            rm.rmsmp_debug_set_wave_split(*request)
+            out = {}
+            for kind in (rm.OUT_INT32, rm.OUT_U4):
+                Ys, eps = [], []
+                for R in (A, Bl):
+                    if kind == rm.OUT_INT32:
+                        Ys.append(torch.full((R["M"], R["N"]), -777, dtype=torch.int32, device=DEV))
+                        eps.append(rm.make_epilogue(R["s_x"], 0, 4, None, False, kind))
+                    else:
+                        Ys.append(torch.full((R["N"], R["M"] // 2), 0xEE, dtype=torch.uint8, device=DEV))
+                        eps.append(rm.make_epilogue(R["s_x"], 0, 4, None, True, kind, R["inv"]))
+                rm.rmsmp_conv2d_pair(A["p"], A["d"], eps[0], Ys[0], Bl["p"], Bl["d"], eps[1], Ys[1], X)
+                if request != (0, 0, 0, 0) or kind == rm.OUT_U4:  # (the choice is the one for 4-bit output)
+                    assert rm.rmsmp_debug_last_dispatch() == ("lds_resident_pair", record), request
+                out[kind] = Ys
+            torch.cuda.synchronize()
+            _check_samples(A, out[rm.OUT_INT32][0], out[rm.OUT_U4][0])
+            _check_samples(Bl, out[rm.OUT_INT32][1], out[rm.OUT_U4][1])
+    finally:
+        rm.rmsmp_debug_set_wave_split(0, 0, 0, 0)
+    A["p"].free()
+    Bl["p"].free()
+    torch.cuda.empty_cache()
+
+
 @pytest.mark.parametrize("idx", range(len(si.RESNET18_CONVS)))
 def test_config3_resnet18_layer_batch64_sampled(rm, oracle, idx):
     """Every convolution of the ResNet-18 stack at batch 64 and 224x224 input geometry against the
