@@ -550,6 +550,9 @@ def main():
     dom_ops = sum(L["ops"] for u in dom_units for L in u["layers"]) / len(dom_units)
     dom_layers = [L for u in dom_units for L in u["layers"]]
     achieved = dom_ops / dom_us / 1e6
+    # what the kernel's own matrix instruction reaches with nothing around it: most layers run on the 6-bit one, twice the int8 rate
+    six_bit = "fp6" in dom_name
+    own_rate = rm.rmsmp_debug_measure_mfma6() if six_bit else rm.rmsmp_debug_measure_peaks()[0]
 
     out = {
         "metric": "effective int TOPS of row-wise mixed-scheme GEMM (% int8 MFMA peak), 1 GPU",
@@ -566,6 +569,8 @@ def main():
                    "gpu_events_ms_per_step": round(gpu_ms / args.steps, 6)},
         "roofline": {"bound": "mfma", "achieved": round(achieved, 2), "peak": INT8_MFMA_PEAK_TOPS, "unit": "TOP/s",
                      "frac": round(achieved / INT8_MFMA_PEAK_TOPS, 4), "traffic": traffic_from_profile(dom_name),
+                     "instruction": "6-bit" if six_bit else "int8", "measured_rate_of_instruction": round(own_rate, 1),
+                     "frac_of_instruction_rate": round(achieved / own_rate, 4),
                      "kernel": dom_name, "avg_launch_us": round(dom_us, 3), "gop_per_launch": round(dom_ops / 1e9, 3),
                      "layers": [L["name"] for L in dom_layers], "time_share_by_kernel": share},
         "per_layer": per_layer,
