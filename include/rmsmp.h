@@ -95,11 +95,16 @@ rmsmp_status rmsmp_pack_weights(const float* W, int64_t M, int64_t K, const uint
  * rmsmp_pack_weights with storage options.  flags = 0 is rmsmp_pack_weights.
  *   RMSMP_PACK_POT_AS_INT8  PoT-4 rows are stored decoded, one byte per weight (their level
  *       2^(6-k) or 0, signed), like Fixed-8 rows: the same levels, scales and results bit for
- *       bit, twice the weight bytes for those rows, and no table decode in the K loop.  On
- *       matrix cores a PoT row multiplies at the same rate as any other and only its decode
- *       costs (the opposite of Section 4's FPGA, where PoT rows are the cheap ones), so this
- *       pays for compute-bound layers -- convolutions, GEMMs with many columns -- and costs
- *       bandwidth where the weights are the traffic (N <= 64).
+ *       bit, twice the weight bytes for those rows, and no table decode in the K loop of the
+ *       int8 kernels.  On matrix cores a PoT row multiplies at the same rate as any other and only
+ *       its decode costs (the opposite of Section 4's FPGA, where PoT rows are the cheap ones).
+ *       Most layers run on the operand form (see RMSMP_PACK_NO_OPERAND_FORM), which has no decode:
+ *       there the flag gains nothing, and costs time where the layer has Fixed-8 rows, whose
+ *       blocks the PoT rows then share and which are multiplied twice (3x3, 144 channels, 16 x 57 x 57,
+ *       35:60:5, 13.9 -> 17.7 us).  It gains on layers that the int8 kernels have then (3x3,
+ *       256 channels, 32 x 14 x 14, 7.9 -> 7.2 us); a ResNet-18 stack at batch 64 takes the same
+ *       at 35:60:5 and 3 % longer at 60:35:5.  It costs bandwidth where the weights are the traffic
+ *       (N <= 64).  For programs that leave the operand form out it gains on compute-bound layers.
  *   RMSMP_PACK_NO_OPERAND_FORM  only the packed blob is kept on the device.  Without this flag a
  *       layer is stored a second time as operands of the 6-bit matrix instructions, which calls
  *       with 4-bit activations and more than 64 columns run on where they are the faster way: 0.75
@@ -308,7 +313,8 @@ rmsmp_status rmsmp_ste_backward(const float* W, const float* alpha, const float*
  *   10..13 a work-group shape of the skinny kernel, 14 and 15 two more of the tile kernel, 16..19 the split kernel
  *   on half weight tiles with 4 or 8 waves and 16 (16, 17) or 32 columns (18, 19; also for a pair), 20..24 a shape of the tile
  *   kernel with neighbouring tiles joined in a wave (layers with Fixed-8 rows, no GELU; 1 elsewhere), 32..41 a shape of
- *   the patch kernel (convolutions of several taps that it fits, no GELU; the automatic choice elsewhere; 32..34 also for a pair),
+ *   the patch kernel (convolutions of several taps that it fits, no GELU; the automatic choice elsewhere; 32..34 also for a pair;
+ *   a pair that is asked for in any other number of 1..31 goes to half tiles where those are fast, else to the int8 launch of both or two launches),
  *   4, 8 and 16 that many rows of the first-layer kernel's tiles;
  *   side_by_side = 1 instead: the int8 kernels only
  *   (a convolution that needs a workspace is then lowered into it), 2: the general kernel only.

@@ -9,9 +9,10 @@
 // with zero weights, and what lies there in memory does not matter.  Taps outside the image read a block that holds the zero
 // point.
 //
-// Measured, weights warm, back to back, the kernel that had the layer before / this one: 64 images of a ResNet-18's 3x3 layers, 64 channels of 56 x 56 12.1 / 11.4 us,
-// 128 of 28 x 28 12.0 / 9.8, 256 of 14 x 14 10.9 / 10.0, 512 of 7 x 7 11.6 / 10.4 (int8, LDS-resident); 144 channels of 16 x 57 x 57
-// 16.9 / 13.0 (tile kernel); the heads of 64 and 256 channels with their 1x1 layers 12.6 / 12.0 and 12.4 / 8.7.
+// Measured, weights warm, back to back, the kernel that had the layer before / this one: 64 images of a ResNet-18's 3x3 layers, 64 channels of 56 x 56 12.3 / 11.7 us
+// (11.3-11.8 / 11.5-11.7 in the benchmark's loop on several cards: no gain), 128 of 28 x 28 12.4 / 10.2, 256 of 14 x 14 11.2 / 10.4 (10.5 / 10.1-10.5), 512 of
+// 7 x 7 11.8 / 10.5 (int8, LDS-resident); 144 channels of 16 x 57 x 57 with a bias 18.8 / 13.9 (tile kernel); the heads of 64 and 256 channels with their
+// 1x1 layers 12.4 / 12.1 and 12.4 / 8.9.
 // What bounds it: a launch is one round of work-groups, each a chain of phases (clock stamps, 128 channels of 28 x 28, 64 x 256 outputs, of
 // 18 600 cycles): 500 until the first reads are out, 1 500 more for the weights' first reads, 2 300 until the patch is in LDS, 8 700
 // multiplying (5 800 at the matrix cores' rate), 5 400 of vector instructions for the 4-bit codes; and 2 us of launch.  With 32 columns x 2
